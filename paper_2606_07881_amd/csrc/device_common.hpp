@@ -319,6 +319,13 @@ template <> struct AccPerm<bf16> { typedef StepPairPerm type; };
 __device__ __forceinline__ void dma16(const void* g, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(lds) : "memory", "m0");
 }
+// The same from a wave-uniform base address and a 32-bit byte offset per lane,
+// to LDS byte address lds + IMM: three instructions.
+template <int IMM> __device__ __forceinline__ void dma16s(const void* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_add_u32 m0, %1, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %3" ::"v"(off), "s"(lds), "n"(IMM),
+               "s"(base)
+               : "memory", "m0", "scc");
+}
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");

@@ -619,9 +619,10 @@ __device__ __forceinline__ void ce_stats_panel(const GemmArgs& a, const float* c
 // covers whole 256-byte row segments with each store, and each atomic add
 // covers 64 consecutive floats. Tiles larger than the ring are done in row
 // panels of PR rows.
-template <typename TO, int EPI, class CF, bool PRE, int N_I, int N_J>
-__device__ __forceinline__ void staged_epilogue(const GemmArgs& a, float* cl, int m0, int n0, int wm0, int wn0,
-                                                const floatx4 (&acc)[N_I][N_J],
+// CF gives BM, BN, NT, PR and LDC; put(p) writes this wave's accumulators of
+// panel p (rows p * PR ..) into the panel, row stride LDC.
+template <typename TO, int EPI, class CF, bool PRE, class Put>
+__device__ __forceinline__ void staged_epilogue(const GemmArgs& a, float* cl, int m0, int n0, Put&& put,
                                                 const u32x4 (&pre)[EpiGeom<TO, CF::BN, CF::PR, CF::NT>::P],
                                                 const float (&pb)[16 / sizeof(TO)]) {
   constexpr int BM = CF::BM, BN = CF::BN, NT = CF::NT, LDC = CF::LDC, PR = CF::PR;
@@ -638,14 +639,7 @@ __device__ __forceinline__ void staged_epilogue(const GemmArgs& a, float* cl, in
     u32x4 pre_p[PANEL_AUX ? EpiGeom<TO, BN, PR, NT>::P : 1];
     if constexpr (PANEL_AUX) prefetch_aux<TO, BN, PR, NT>(a, m0 + p * PR, n0, tid, pre_p);
     __syncthreads();   // every wave is done with the ring (or with the previous panel)
-    if (wm0 >= p * PR && wm0 < (p + 1) * PR) {
-#pragma unroll
-      for (int i = 0; i < N_I; ++i)
-#pragma unroll
-        for (int j = 0; j < N_J; ++j)
-          *reinterpret_cast<floatx4*>(cl + (wm0 - p * PR + i * 16 + (l & 15)) * LDC + wn0 + j * 16 + 4 * (l >> 4)) =
-              acc[i][j];
-    }
+    put(p);
     __syncthreads();
     const int mb = m0 + p * PR;
     if constexpr (EPI == EPI_CE_STATS) {
@@ -687,6 +681,50 @@ __device__ __forceinline__ void staged_epilogue(const GemmArgs& a, float* cl, in
   }
 }
 
+__device__ __forceinline__ const void* uniform_ptr(const void* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = __builtin_amdgcn_readfirstlane((int)(v >> 32));
+  return reinterpret_cast<const void*>((uint64_t)hi << 32 | lo);
+}
+// This workgroup's output tile. Grouped weight gradients (GRP): its problem is
+// found with wave-uniform scalar loads and put into `a`; false for the padding
+// workgroups past a problem's tiles.
+template <int BM, int BN, bool GRP>
+__device__ __forceinline__ bool locate_tile(GemmArgs& a, int& m0, int& n0) {
+  int pid = blockIdx.x;
+  int xcd_m = 0;   // grouped weight gradients: XCD blocks of the tile grid (0: generic order)
+  if constexpr (GRP) {
+    int p = 0;
+    while (p + 1 < a.group_n && pid >= a.group[p + 1].tile0) ++p;
+    const WgradProblem& pr = a.group[p];
+    pid -= __builtin_amdgcn_readfirstlane(pr.tile0);
+    xcd_m = __builtin_amdgcn_readfirstlane(pr.xcd_m);
+    a.A = uniform_ptr(pr.A);   // in scalar registers, whichever way they were loaded
+    a.B = uniform_ptr(pr.B);
+    a.C = pr.C;
+    a.M = __builtin_amdgcn_readfirstlane(pr.M);
+    a.N = __builtin_amdgcn_readfirstlane(pr.N);
+    a.lda = a.M;
+    a.ldb = a.N;
+    a.ldc = a.N;
+    if (pid >= ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN)) return false;   // padding to a multiple of 8
+  }
+  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
+  int tm, tn;
+  if (xcd_m > 0) {
+    // XCD x = pid % 8 takes block (x % xcd_m, x / xcd_m) of bm x bn tiles, column by column
+    const int x = pid & 7, k = pid >> 3;
+    const int bm = tiles_m / xcd_m, bn = tiles_n / (8 / xcd_m);
+    tm = (x % xcd_m) * bm + k % bm;
+    tn = (x / xcd_m) * bn + k / bm;
+  } else {
+    tile_coords(pid, tiles_m, tiles_n, tm, tn);
+  }
+  m0 = tm * BM;
+  n0 = tn * BN;
+  return true;
+}
+
 // Scheduling pattern for one MFMA step: NREAD LDS reads (of the next step)
 // spread evenly between NMFMA independent MFMAs (of this step).
 template <int NREAD, int NMFMA>
@@ -707,38 +745,8 @@ __global__ void __launch_bounds__(CF::NT, CF::OCC) gemm_pipe_kernel(GemmArgs a, 
   constexpr int L = CF::LA + CF::LB;
   __shared__ u32x4 smem[CF::SMEM_SLOTS];
   const int tid = threadIdx.x, l = lane_id(), w = tid >> 6;
-  int pid = blockIdx.x;
-  int xcd_m = 0;   // grouped weight gradients: XCD blocks of the tile grid (0: generic order)
-  if constexpr (GRP) {
-    // grouped weight gradients: find this workgroup's problem (wave-uniform scalar loads)
-    int p = 0;
-    while (p + 1 < a.group_n && pid >= a.group[p + 1].tile0) ++p;
-    const WgradProblem& pr = a.group[p];
-    pid -= pr.tile0;
-    const int tm_all = (pr.M + BM - 1) / BM, tn_all = (pr.N + BN - 1) / BN;
-    if (pid >= tm_all * tn_all) return;   // padding to a multiple of 8
-    xcd_m = pr.xcd_m;
-    a.A = pr.A;
-    a.B = pr.B;
-    a.C = pr.C;
-    a.M = pr.M;
-    a.N = pr.N;
-    a.lda = pr.M;
-    a.ldb = pr.N;
-    a.ldc = pr.N;
-  }
-  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
-  int tm, tn;
-  if (xcd_m > 0) {
-    // XCD x = pid % 8 takes block (x % xcd_m, x / xcd_m) of bm x bn tiles, column by column
-    const int x = pid & 7, k = pid >> 3;
-    const int bm = tiles_m / xcd_m, bn = tiles_n / (8 / xcd_m);
-    tm = (x % xcd_m) * bm + k % bm;
-    tn = (x / xcd_m) * bn + k / bm;
-  } else {
-    tile_coords(pid, tiles_m, tiles_n, tm, tn);
-  }
-  const int m0 = tm * BM, n0 = tn * BN;
+  int m0, n0;
+  if (!locate_tile<BM, BN, GRP>(a, m0, n0)) return;
   const int k_begin = blockIdx.y * k_per_split;
   const int k_end = min(a.K, k_begin + k_per_split);
   const int nk = (k_end - k_begin + BKE - 1) / BKE;
@@ -814,10 +822,8 @@ __global__ void __launch_bounds__(CF::NT, CF::OCC) gemm_pipe_kernel(GemmArgs a, 
   u32x4 pre[EpiGeom<TO, BN, CF::PR, NT>::P];
   if constexpr (PRE) prefetch_aux<TO, BN, CF::PR, NT>(a, m0, n0, tid, pre);
   float pb[16 / sizeof(TO)];
-  // (tall wave tiles load it after the loop: their registers are taken by the fragments)
   constexpr bool HAS_BIAS = EPI == EPI_BIAS || EPI == EPI_BIAS_RES || EPI == EPI_BIAS_GELU;
-  constexpr bool TALL = WM / 16 >= 8;
-  if constexpr (HAS_BIAS && !TALL) prefetch_bias<TO, BN, CF::PR, NT>(a, n0, tid, pb);
+  if constexpr (HAS_BIAS) prefetch_bias<TO, BN, CF::PR, NT>(a, n0, tid, pb);
 
   // Fragments are double-buffered in registers: the LDS reads of the next
   // MFMA step are issued before the MFMAs of the current one. The barrier that
@@ -915,62 +921,499 @@ __global__ void __launch_bounds__(CF::NT, CF::OCC) gemm_pipe_kernel(GemmArgs a, 
       st0 = st1;
     }
   };
-  // Tall wave tiles (WM = 128: eight A fragments per step, 128 accumulator
-  // VGPRs) fit two wavefronts per SIMD only with the A fragments single-
-  // buffered: each is re-read for the next step right after its row's MFMAs
-  // have issued, so its register is reused (B stays double-buffered). The
-  // ring, barriers and waits are those of the loop above; the refill loads
-  // are spread one or more per A row.
-  constexpr int G = WM / 16;
-  auto main_loop_tall = [&](auto kf) {
+  if (kfull) main_loop(std::true_type{});
+  else main_loop(std::false_type{});
+  wait_vmcnt<0>();   // the fills past the last tile, before the ring is reused
+  float* cl = reinterpret_cast<float*>(smem);
+  auto put = [&](int p) {
+    if (wm0 < p * CF::PR || wm0 >= (p + 1) * CF::PR) return;
 #pragma unroll
-    for (int t = 0; t < NS; ++t) fill(kf, t, t);
-    wait_vmcnt<L * (NS - 1)>();
-    barrier_no_fence();
-    read_step(0, 0, ya, xa);
-    int st0 = 0;
-    for (int kt = 0; kt < nk; ++kt) {
-      const int st1 = st0 + 1 == NS ? 0 : st0 + 1;
-      wait_lds_reads();   // ya/xa of step 0 of tile kt
+    for (int i = 0; i < WM / 16; ++i)
 #pragma unroll
-      for (int j = 0; j < WN / 16; ++j) read_frag(st0, 1, G + j, ya, xb);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int j = 0; j < WN / 16; ++j)
+        *reinterpret_cast<floatx4*>(cl + (wm0 - p * CF::PR + i * 16 + (l & 15)) * CF::LDC + wn0 + j * 16 + 4 * (l >> 4)) =
+            acc[i][j];
+  };
+  staged_epilogue<TO, EPI, CF, PRE>(a, cl, m0, n0, put, pre, pb);
+}
+
+// ============================================================================================
+// bf16 ping-pong kernel: 256 x BN output tiles (BN = 256 or 128), 8 wavefronts.
+//
+// The wavefronts form two groups of four, one wavefront of each group per SIMD.
+// Time runs in slots that end in a workgroup barrier; a wavefront alternates a
+// memory slot (the LDS reads of its next 16 MFMAs, two or three direct-to-LDS
+// loads of a later k-tile) with a matrix slot (those 16 MFMAs), and the groups
+// are one slot apart, so in every slot one wavefront of each SIMD feeds the
+// matrix cores while the other one reads and loads. A loop in which all eight
+// wavefronts read, wait and multiply together left the matrix cores idle for
+// half of the time (the waits of both wavefronts of a SIMD fell together).
+//
+// A k-tile is 64 contracted elements. Operands are kept in LDS as sub-tiles of
+// 128 rows (16 KB), the layouts of the ring above: K-major [128][8 chunks],
+// MN-major [64 k][128]. A wavefront's rows are two pieces, one per A sub-tile h
+// (rows 128 h + 64 wm .. at BN = 256, 128 h + 32 wm .. at 128), so that an
+// A sub-tile is read in one memory slot and refilled from the next one on.
+//
+// BN = 256 (2 x 4 wavefronts, four slot pairs per k-tile, two LDS stages):
+//   pair 0: A_0 read     A_0 B_0     pair 1: B_1 read       A_0 B_1
+//   pair 2: A_1 read     A_1 B_1     pair 3: next B_0 read  A_1 B_0
+// 8, 4, 8 and 4 LDS reads per slot. The B fragments alternate between two
+// register sets. Refills of k-tile t's stage with tile t + 2: B_0 in pair 1,
+// A_0 in 2, B_1 in 3, A_1 in pair 0 of tile t + 1.
+// BN = 128 (4 x 2 wavefronts, two pairs per k-tile, three A and four B stages):
+//   pair 0: A_0, half of the next B read  A_0 B    pair 1: A_1, other half  A_1 B
+// Refills: A_0 of tile t + 2 and half of B of t + 3 in pair 0, A_1 of t + 2 and
+// half of B of t + 4 in pair 1.
+//
+// What bounds it: at 256 x 256 the loop runs at 93% of the MFMA issue rate
+// (2205 cycles per k-tile against 2048; the ring kernel's 8-wavefront tiles
+// took about 4200), and on random data the card then lowers its clock to
+// 1.6-1.9 GHz: 1270 -> 1500 TFLOP/s on an 8192^3 product, where zeros run at
+// 2.36 GHz and 1830. 256 x 128 tiles reach 1290 cycles against 1024 in the same
+// product, but in the stage their loads come from beyond L2 and the deeper
+// prefetch of the ring kernel wins (qkv 67 against 68-74 us), so only the
+// window products, whose operands are long, take them (207 -> 196 us at
+// 3072 x 768 x 32768).
+//
+// Ordering. A wavefront waits for its LDS reads at the start of the matrix slot
+// that follows them, so a sub-tile read by group 1 in slot s (group 0 is one
+// slot earlier) is free for refills from slot s + 2 on, which is where the
+// refills above are issued. Loads are waited for (vmcnt, in order) one memory
+// slot before their first read, that is four (BN 256) or three (BN 128) memory
+// slots after their issue, and a barrier lies between the wait and the read.
+// ============================================================================================
+template <int BN_> struct PP {
+  static constexpr int BM = 256, BN = BN_, NT = 512;
+  static constexpr int WR = BN == 256 ? 2 : 4, WC = 8 / WR;       // wavefront grid
+  static constexpr int NH = BN / 128;                             // B sub-tiles
+  static constexpr int TI = 128 / WR / 16, TJ = 128 / WC / 16;    // 16 x 16 tiles per wavefront and sub-tile pair
+  static constexpr int SUB = 1024;                                // 16-byte slots per sub-tile
+  static constexpr int SA = BN == 256 ? 2 : 3, SB = BN == 256 ? 2 : 4;   // LDS stages of A and of B
+  static constexpr int RING = (SA * 2 + SB * NH) * SUB;
+  static constexpr int LDC = BN + 4, PR = BN == 256 ? 128 : 256;  // epilogue panels
+  static constexpr int SMEM_SLOTS = RING > PR * LDC / 4 ? RING : PR * LDC / 4;
+};
+template <int H> struct IC { static constexpr int value = H; };
+
+// The loads of one operand: each sub-tile is 16 wave loads of 64 slots, two per
+// wavefront. off: byte offset of load p of sub-tile h from the tile's base at
+// the k-tile's first contracted element, rows past the operand clamped into it
+// (they feed outputs that are not stored).
+template <bool KMAJ, int NH>
+struct PPOperand {
+  static constexpr int NP = KMAJ ? 2 : 1;   // (MN-major: load 1 is 32 lines after load 0, no clamping between them)
+  uint32_t off[NH][NP];
+  const bf16* base;   // the tile's first row or column at contracted element 0 (uniform)
+  int64_t ld;
+  int kk;             // K-major: this thread's first contracted element in the k-tile; else its line of load 0
+
+  __device__ __forceinline__ void init(const bf16* src, int64_t ld_, int row0, int rows_total, int w, int l) {
+    ld = ld_;
+    if (KMAJ) {
+      base = src + (int64_t)row0 * ld;
+      kk = 8 * ((l & 7) ^ (((w & 1) * 4 + (l >> 4)) & 7));
+    } else {
+      base = src + row0;
+      kk = w * 4 + (l >> 4);
+    }
 #pragma unroll
-      for (int i = 0; i < G; ++i) {
+    for (int h = 0; h < NH; ++h)
 #pragma unroll
-        for (int j = 0; j < WN / 16; ++j) mma_step<bf16>(acc[i][j], xa[j], ya[i]);
-        read_frag(st0, 1, i, ya, xb);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int p = 0; p < NP; ++p) {
+        if (KMAJ) {
+          const int row = min(row0 + h * 128 + p * 64 + w * 8 + (l >> 3), rows_total - 1) - row0;
+          off[h][p] = (uint32_t)(2 * (row * ld + kk));
+        } else {
+          const int c = (l & 15) ^ trt_swz<128>(kk);
+          const int col = min(row0 + h * 128 + c * 8, (rows_total - 1) & ~7) - row0;
+          off[h][p] = (uint32_t)(2 * (kk * ld + col));
+        }
       }
-      wait_lds_reads();   // ya/xb of step 1
-      wait_vmcnt<L * (NS - 2)>();
-      barrier_no_fence();
-#pragma unroll
-      for (int j = 0; j < WN / 16; ++j) read_frag(st1, 0, G + j, ya, xa);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < G; ++i) {
-#pragma unroll
-        for (int p = i * L / G; p < (i + 1) * L / G; ++p) fill_one(kf, kt + NS, st0, p);
-#pragma unroll
-        for (int j = 0; j < WN / 16; ++j) mma_step<bf16>(acc[i][j], xb[j], ya[i]);
-        read_frag(st1, 0, i, ya, xa);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      st0 = st1;
+  }
+  // elements from contracted element 0 to k
+  __device__ __forceinline__ int64_t at(int k) const { return KMAJ ? (int64_t)k : (int64_t)k * ld; }
+  // Load P of sub-tile H of the k-tile whose first contracted element is at g,
+  // to LDS byte address lds + IMM + (8 P) KB, lds including this wavefront's KB.
+  template <int H, int P, int IMM> __device__ __forceinline__ void load(const bf16* g, uint32_t lds) const {
+    dma16s<IMM + P * 8192>(KMAJ ? g : g + P * 32 * ld, off[H][KMAJ ? P : 0], lds);
+  }
+  // The same for a k-tile with only `valid` contracted elements inside K: slots
+  // past them come from the zero page.
+  template <int H, int P, int IMM>
+  __device__ __forceinline__ void load_tail(const bf16* g, uint32_t lds, int valid, const void* zeros) const {
+    const bool ok = KMAJ ? kk < valid : kk + 32 * P < valid;
+    const void* q = reinterpret_cast<const char*>(KMAJ ? g : g + P * 32 * ld) + off[H][KMAJ ? P : 0];
+    dma16(ok ? q : zeros, lds + IMM + P * 8192);
+  }
+};
+
+template <typename TO, bool AK, bool BK, int EPI, int BN_, bool GRP = false>
+__global__ void __launch_bounds__(512, 2) gemm_pp_kernel(GemmArgs a, int k_per_split) {
+  using CF = PP<BN_>;
+  constexpr int BM = CF::BM, BN = CF::BN, NT = CF::NT, TI = CF::TI, TJ = CF::TJ, NH = CF::NH, SUB = CF::SUB;
+  __shared__ u32x4 smem[CF::SMEM_SLOTS];
+  const int tid = threadIdx.x, l = lane_id();
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), group = w >> 2;
+  int m0, n0;
+  if (!locate_tile<BM, BN, GRP>(a, m0, n0)) return;
+  const int k_begin = blockIdx.y * k_per_split;
+  const int k_end = min(a.K, k_begin + k_per_split);
+  const int nk = (k_end - k_begin + 63) / 64;
+  const int wm = w / CF::WC, wn = w % CF::WC;
+
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) u32x4*)smem);
+  const uint32_t ldsw = lds0 + (uint32_t)w * 1024;
+  PPOperand<AK, 2> oa;
+  PPOperand<BK, NH> ob;
+  oa.init(reinterpret_cast<const bf16*>(a.A), a.lda, m0, a.M, w, l);
+  ob.init(reinterpret_cast<const bf16*>(a.B), a.ldb, n0, a.N, w, l);
+  // sub-tile h of A or B in LDS stage st, in slots from the start
+  auto slot_a = [](int st, int h) { return (st * 2 + h) * SUB; };
+  auto slot_b = [](int st, int h) { return (CF::SA * 2 + st * NH + h) * SUB; };
+  // Contracted position of the next fills of A and of B: their addresses advance
+  // by one k-tile at a time. B may come in segments of seg_rows contracted rows
+  // (weight gradients; a k-tile never straddles two).
+  const bf16* pa = oa.base + oa.at(k_begin);
+  const bf16* pb_ = ob.base;
+  const int64_t step_a = oa.at(64), step_b = ob.at(64);
+  int seg_left = 0, seg = 0;
+  const bool segs = !AK && !BK && !GRP && a.seg_rows > 0;   // uniform
+  if (segs) {
+    const int sg = k_begin / (int)a.seg_rows, r = k_begin - sg * (int)a.seg_rows;
+    seg = (a.seg_first + sg) % a.seg_count;
+    seg_left = (int)a.seg_rows - r;
+    pb_ += (int64_t)seg * a.seg_stride + (int64_t)r * a.ldb;
+  } else {
+    pb_ += ob.at(k_begin);
+  }
+  auto next_a = [&] { pa += step_a; };
+  auto next_b = [&] {
+    pb_ += step_b;
+    if (segs && (seg_left -= 64) <= 0) {
+      seg = seg + 1 == a.seg_count ? 0 : seg + 1;
+      seg_left = (int)a.seg_rows;
+      pb_ = ob.base + (int64_t)seg * a.seg_stride;
     }
   };
-  if constexpr (TALL) {
-    if (kfull) main_loop_tall(std::true_type{});
-    else main_loop_tall(std::false_type{});
-  } else {
-    if (kfull) main_loop(std::true_type{});
-    else main_loop(std::false_type{});
+  const int nfull = (k_end - k_begin) / 64;   // k-tiles wholly inside K
+  // Load of k-tile kt: in the main loop (FULL) it lies wholly inside K; else it
+  // may be the partial last one, or lie past the end (no load then).
+  auto load_a = [&](auto full, int kt, uint32_t lds, auto h, auto p, auto imm) {
+    if (decltype(full)::value || kt < nfull) oa.template load<h.value, p.value, imm.value>(pa, lds);
+    else if (kt < nk) oa.template load_tail<h.value, p.value, imm.value>(pa, lds, k_end - k_begin - nfull * 64, a.zeros);
+  };
+  auto load_b = [&](auto full, int kt, uint32_t lds, auto h, auto p, auto imm) {
+    if (decltype(full)::value || kt < nfull) ob.template load<h.value, p.value, imm.value>(pb_, lds);
+    else if (kt < nk) ob.template load_tail<h.value, p.value, imm.value>(pb_, lds, k_end - k_begin - nfull * 64, a.zeros);
+  };
+  floatx4 acc[2][NH][TI][TJ];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int g = 0; g < NH; ++g)
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) acc[h][g][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  // The bf16 residual or gelu'(u) rows of a one-panel epilogue and the bias, in
+  // registers by the epilogue. They are loaded after the last k-tile's loads
+  // have been issued: vmcnt counts in order, so loaded at the start the first
+  // k-tile would wait for them (measured 1.6 us for the bias and 3.2 us with the
+  // residual rows, of a 25 us product), and in the middle a later one would.
+  constexpr bool PRE = (EPI == EPI_BIAS_RES || EPI == EPI_GELU_GRAD) && sizeof(TO) == 2 && CF::PR == BM;
+  constexpr bool HAS_BIAS = EPI == EPI_BIAS || EPI == EPI_BIAS_RES || EPI == EPI_BIAS_GELU;
+  using EG = EpiGeom<TO, BN, CF::PR, NT>;
+  u32x4 pre[EG::P];
+  float pb[EG::U];
+  // n_late: the loads in flight behind the k-tiles' when they were all issued
+  // unconditionally (a whole tile, aligned), else 0 (the waits then cover them)
+  constexpr int N_LATE = (PRE ? EG::P : 0) + (HAS_BIAS ? EG::U / 4 : 0);
+  auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
+  const bool whole = m0 + BM <= a.M && n0 + BN <= a.N && (!PRE || (a.ld_aux % 8 == 0 && al16(a.aux))) &&
+                     (!HAS_BIAS || al16(a.bias));   // uniform
+  const int n_late = whole ? N_LATE : 0;
+  auto late_loads = [&] {
+    if constexpr (N_LATE > 0) {
+      if (whole) {
+        const int n = n0 + (tid % EG::UPR) * EG::U, r0 = tid / EG::UPR;
+        if constexpr (PRE) {
+#pragma unroll
+          for (int p = 0; p < EG::P; ++p)
+            pre[p] = ld16g(reinterpret_cast<const bf16*>(a.aux) + (int64_t)(m0 + r0 + p * EG::RPI) * a.ld_aux + n);
+        }
+        if constexpr (HAS_BIAS) {
+#pragma unroll
+          for (int q = 0; q < EG::U / 4; ++q) {
+            const u32x4 v = ld16g(a.bias + n + 4 * q);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pb[4 * q + j] = vget<float>(v, j);
+          }
+        }
+      } else {
+        if constexpr (PRE) prefetch_aux<TO, BN, CF::PR, NT>(a, m0, n0, tid, pre);
+        if constexpr (HAS_BIAS) prefetch_bias<TO, BN, CF::PR, NT>(a, n0, tid, pb);
+      }
+    }
+  };
+
+  // Wait until at most n loads are outstanding: n in the main loop, and in the
+  // last k-tiles (left = 1 for the last, 2, ..), where later loads are not
+  // issued, n less those (l1, l2, ..). late: the epilogue's loads behind them.
+  auto wait_but = [&](auto full, auto n, int late, int left, int l1, int l2, int l3 = -1, int l4 = -1) {
+    if constexpr (decltype(full)::value) {
+      wait_vmcnt<n.value>();
+    } else {
+      const int m = left <= 1 ? l1 : left == 2 ? l2 : left == 3 && l3 >= 0 ? l3 : left == 4 && l4 >= 0 ? l4 : n.value;
+      if (late > 0) {   // (a smaller count waits for more)
+        if (m >= 10) wait_vmcnt<10 + N_LATE>();
+        else if (m >= 8) wait_vmcnt<8 + N_LATE>();
+        else if (m >= 6) wait_vmcnt<6 + N_LATE>();
+        else if (m >= 4) wait_vmcnt<4 + N_LATE>();
+        else if (m >= 2) wait_vmcnt<2 + N_LATE>();
+        else wait_vmcnt<N_LATE>();
+        return;
+      }
+      switch (m) {
+        case 10: wait_vmcnt<10>(); break;
+        case 9: wait_vmcnt<9>(); break;
+        case 8: wait_vmcnt<8>(); break;
+        case 7: wait_vmcnt<7>(); break;
+        case 6: wait_vmcnt<6>(); break;
+        case 4: wait_vmcnt<4>(); break;
+        case 2: wait_vmcnt<2>(); break;
+        default: wait_vmcnt<0>(); break;
+      }
+    }
+  };
+
+  // fragment addresses: K-major, this lane's slot for step s of row 0 of the
+  // sub-tile (16 rows further are 128 slots); MN-major, byte offset per fragment
+  int ka[2], kb[2];   // (K-major)
+  uint32_t ta[TI], tb[TJ];   // (MN-major)
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    ka[s] = kmaj_slot(wm * 16 * TI + (l & 15), s * 4 + (l >> 4));
+    kb[s] = kmaj_slot(wn * 16 * TJ + (l & 15), s * 4 + (l >> 4));
   }
-  wait_vmcnt<0>();   // the fills past the last tile, before the ring is reused
-  if constexpr (HAS_BIAS && TALL) prefetch_bias<TO, BN, CF::PR, NT>(a, n0, tid, pb);
-  staged_epilogue<TO, EPI, CF, PRE>(a, reinterpret_cast<float*>(smem), m0, n0, wm0, wn0, acc, pre, pb);
+#pragma unroll
+  for (int i = 0; i < TI; ++i) ta[i] = AK ? 0u : lds_frag_tr_off<128>((wm * TI + i) * 16);
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) tb[j] = BK ? 0u : lds_frag_tr_off<128>((wn * TJ + j) * 16);
+  auto frag_a = [&](int slot, int i, int s) -> u32x4 {
+    if constexpr (AK) return smem[slot + ka[s] + i * 128];
+    else return lds_frag_tr_at<128>(lds0 + 16 * slot + ta[i], s);
+  };
+  auto frag_b = [&](int slot, int j, int s) -> u32x4 {
+    if constexpr (BK) return smem[slot + kb[s] + j * 128];
+    else return lds_frag_tr_at<128>(lds0 + 16 * slot + tb[j], s);
+  };
+  u32x4 fa[TI][2], fb0[TJ][2], fb1[TJ][2];
+  auto read_a = [&](int slot) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < TI; ++i) fa[i][s] = frag_a(slot, i, s);
+  };
+  auto read_b = [&](int slot, u32x4 (&f)[TJ][2], int j0, int j1) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j)
+        if (j >= j0 && j < j1) f[j][s] = frag_b(slot, j, s);
+  };
+  auto end_slot = [&] {
+    __builtin_amdgcn_sched_barrier(0);
+    barrier_no_fence();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto matrix_slot = [&](floatx4 (&c)[TI][TJ], const u32x4 (&f)[TJ][2]) {
+    wait_lds_reads();
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) mma_step<bf16>(c[i][j], f[j][s], fa[i][s]);
+    __builtin_amdgcn_s_setprio(0);
+    end_slot();
+  };
+
+  constexpr std::true_type FULL{};
+  constexpr std::false_type TAIL{};
+  if constexpr (BN == 256) {
+    constexpr int SUBB = SUB * 16, STAGE = 2 * SUBB;   // bytes; A's stages, then B's
+    // k-tile kt in stage st (its parity); x holds its B_0 fragments, y receives those of the next one
+    auto late = [&](int kt) { return kt >= nk - 2 ? n_late : 0; };
+    auto ktile = [&](auto full, int kt, auto st, u32x4 (&x)[TJ][2], u32x4 (&y)[TJ][2]) {
+      constexpr int S = decltype(st)::value;
+      constexpr IC<S * STAGE> A0{};
+      constexpr IC<(S ^ 1) * STAGE + SUBB> A1{};
+      constexpr IC<(2 + S) * STAGE> B0{};
+      constexpr IC<(2 + S) * STAGE + SUBB> B1{};
+      read_a(slot_a(S, 0));
+      load_a(full, kt + 1, ldsw, IC<1>{}, IC<0>{}, A1);
+      load_a(full, kt + 1, ldsw, IC<1>{}, IC<1>{}, A1);
+      next_a();
+      if (!decltype(full)::value && kt == nk - 2) late_loads();
+      wait_but(full, IC<10>{}, late(kt), nk - kt, 2, 10);
+      end_slot();
+      matrix_slot(acc[0][0], x);
+
+      read_b(slot_b(S, 1), y, 0, TJ);
+      load_b(full, kt + 2, ldsw, IC<0>{}, IC<0>{}, B0);
+      load_b(full, kt + 2, ldsw, IC<0>{}, IC<1>{}, B0);
+      wait_but(full, IC<10>{}, late(kt), nk - kt, 0, 8);
+      end_slot();
+      matrix_slot(acc[0][1], y);
+
+      read_a(slot_a(S, 1));
+      load_a(full, kt + 2, ldsw, IC<0>{}, IC<0>{}, A0);
+      load_a(full, kt + 2, ldsw, IC<0>{}, IC<1>{}, A0);
+      wait_but(full, IC<10>{}, late(kt), nk - kt, 0, 6);
+      end_slot();
+      matrix_slot(acc[1][1], y);
+
+      read_b(slot_b(S ^ 1, 0), y, 0, TJ);
+      load_b(full, kt + 2, ldsw, IC<1>{}, IC<0>{}, B1);
+      load_b(full, kt + 2, ldsw, IC<1>{}, IC<1>{}, B1);
+      next_b();
+      wait_but(full, IC<10>{}, late(kt), nk - kt, 0, 4);
+      end_slot();
+      matrix_slot(acc[1][0], x);
+    };
+    // the loads of tiles 0 and 1 that the loop does not issue, in the loop's order
+    auto first = [&](int t, auto st) {
+      constexpr int S = decltype(st)::value;
+      load_b(TAIL, t, ldsw, IC<0>{}, IC<0>{}, IC<(2 + S) * STAGE>{});
+      load_b(TAIL, t, ldsw, IC<0>{}, IC<1>{}, IC<(2 + S) * STAGE>{});
+      load_a(TAIL, t, ldsw, IC<0>{}, IC<0>{}, IC<S * STAGE>{});
+      load_a(TAIL, t, ldsw, IC<0>{}, IC<1>{}, IC<S * STAGE>{});
+      load_b(TAIL, t, ldsw, IC<1>{}, IC<0>{}, IC<(2 + S) * STAGE + SUBB>{});
+      load_b(TAIL, t, ldsw, IC<1>{}, IC<1>{}, IC<(2 + S) * STAGE + SUBB>{});
+      if constexpr (S == 0) {
+        load_a(TAIL, t, ldsw, IC<1>{}, IC<0>{}, IC<SUBB>{});
+        load_a(TAIL, t, ldsw, IC<1>{}, IC<1>{}, IC<SUBB>{});
+        next_a();
+      }
+      next_b();
+    };
+    first(0, IC<0>{});
+    first(1, IC<1>{});
+    if (nk < 2) late_loads();
+    wait_but(TAIL, IC<10>{}, late(nk > 1 ? -1 : 0), nk + 1, 0, 4);   // B_0 and A_0 of tile 0
+    end_slot();
+    read_b(slot_b(0, 0), fb0, 0, TJ);
+    if (group == 1) end_slot();
+    int kt = 0;
+    for (; kt + 3 < nfull; kt += 2) {
+      ktile(FULL, kt, IC<0>{}, fb0, fb1);
+      ktile(FULL, kt + 1, IC<1>{}, fb1, fb0);
+    }
+    for (; kt < nk; kt += 2) {
+      ktile(TAIL, kt, IC<0>{}, fb0, fb1);
+      if (kt + 1 < nk) ktile(TAIL, kt + 1, IC<1>{}, fb1, fb0);
+    }
+    if (group == 0) end_slot();
+  } else {
+    constexpr int SUBB = SUB * 16, AST = 2 * SUBB;   // bytes: sub-tile, stage of A
+    const uint32_t ldsb = ldsw + CF::SA * AST;
+    uint32_t sa = 0, sb = 0;   // byte offsets of the stages of A and B of tile kt
+    const bf16* pb3 = pb_;     // B of tile kt + 3 (its second half is loaded one slot pair after the first)
+    auto ktile = [&](auto full, int kt, u32x4 (&x)[TJ][2], u32x4 (&y)[TJ][2]) {
+      const uint32_t sa2 = sa == 0 ? 2 * AST : sa - AST;                          // A of tile kt + 2 (and kt - 1)
+      const uint32_t sb1 = (sb + SUBB) & (4 * SUBB - 1), sb3 = (sb + 3 * SUBB) & (4 * SUBB - 1);
+      const int fra = (int)(sa >> 4), frb = (int)(sb1 >> 4) + CF::SA * 2 * SUB;
+      read_a(fra);
+      read_b(frb, y, 0, TJ / 2);
+      load_a(full, kt + 2, ldsw + sa2, IC<0>{}, IC<0>{}, IC<0>{});
+      load_a(full, kt + 2, ldsw + sa2, IC<0>{}, IC<1>{}, IC<0>{});
+      {
+        const bf16* cur = pb_;
+        pb_ = pb3;
+        load_b(full, kt + 3, ldsb + sb3, IC<0>{}, IC<1>{}, IC<0>{});
+        pb_ = cur;
+      }
+      wait_but(full, IC<9>{}, kt > nk - 3 ? n_late : 0, nk - kt, 0, 4, 7);
+      end_slot();
+      matrix_slot(acc[0][0], x);
+
+      read_a(fra + SUB);
+      read_b(frb, y, TJ / 2, TJ);
+      load_a(full, kt + 2, ldsw + sa2, IC<1>{}, IC<0>{}, IC<SUBB>{});
+      load_a(full, kt + 2, ldsw + sa2, IC<1>{}, IC<1>{}, IC<SUBB>{});
+      load_b(full, kt + 4, ldsb + sb, IC<0>{}, IC<0>{}, IC<0>{});
+      pb3 = pb_;
+      next_a();
+      next_b();
+      if (!decltype(full)::value && kt == nk - 3) late_loads();
+      wait_but(full, IC<9>{}, kt >= nk - 3 ? n_late : 0, nk - kt, 0, 2, 6, 8);
+      end_slot();
+      matrix_slot(acc[1][0], x);
+      sa = sa == 2 * AST ? 0 : sa + AST;
+      sb = sb1;
+    };
+    // the loads the loop does not issue, in its order
+    load_b(TAIL, 0, ldsb, IC<0>{}, IC<0>{}, IC<0>{});
+    load_b(TAIL, 0, ldsb, IC<0>{}, IC<1>{}, IC<0>{});
+    next_b();
+    load_b(TAIL, 1, ldsb, IC<0>{}, IC<0>{}, IC<SUBB>{});
+    load_a(TAIL, 0, ldsw, IC<0>{}, IC<0>{}, IC<0>{});
+    load_a(TAIL, 0, ldsw, IC<0>{}, IC<1>{}, IC<0>{});
+    load_b(TAIL, 1, ldsb, IC<0>{}, IC<1>{}, IC<SUBB>{});
+    next_b();
+    load_a(TAIL, 0, ldsw, IC<1>{}, IC<0>{}, IC<SUBB>{});
+    load_a(TAIL, 0, ldsw, IC<1>{}, IC<1>{}, IC<SUBB>{});
+    next_a();
+    load_b(TAIL, 2, ldsb, IC<0>{}, IC<0>{}, IC<2 * SUBB>{});
+    load_a(TAIL, 1, ldsw, IC<0>{}, IC<0>{}, IC<AST>{});
+    load_a(TAIL, 1, ldsw, IC<0>{}, IC<1>{}, IC<AST>{});
+    load_b(TAIL, 2, ldsb, IC<0>{}, IC<1>{}, IC<2 * SUBB>{});
+    next_b();
+    load_a(TAIL, 1, ldsw, IC<1>{}, IC<0>{}, IC<AST + SUBB>{});
+    load_a(TAIL, 1, ldsw, IC<1>{}, IC<1>{}, IC<AST + SUBB>{});
+    next_a();
+    load_b(TAIL, 3, ldsb, IC<0>{}, IC<0>{}, IC<3 * SUBB>{});
+    pb3 = pb_;
+    next_b();
+    if (nk < 3) late_loads();
+    wait_but(TAIL, IC<9>{}, nk < 3 ? n_late : 0, nk + 1, 0, 2, 6, 8);   // B of tiles 0 and 1, A_0 of tile 0
+    end_slot();
+    read_b(slot_b(0, 0), fb0, 0, TJ);
+    if (group == 1) end_slot();
+    int kt = 0;
+    for (; kt + 5 < nfull; kt += 2) {
+      ktile(FULL, kt, fb0, fb1);
+      ktile(FULL, kt + 1, fb1, fb0);
+    }
+    for (; kt < nk; kt += 2) {
+      ktile(TAIL, kt, fb0, fb1);
+      if (kt + 1 < nk) ktile(TAIL, kt + 1, fb1, fb0);
+    }
+    if (group == 0) end_slot();
+  }
+  wait_vmcnt<0>();
+  wait_lds_reads();
+  float* cl = reinterpret_cast<float*>(smem);
+  auto put = [&](int p) {   // BN 256: panel p is A sub-tile p; 128: one panel of both
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (CF::PR == 128 && h != p) continue;
+      const int r0 = (CF::PR == 128 ? 0 : h * 128) + wm * 16 * TI + (l & 15);
+#pragma unroll
+      for (int g = 0; g < NH; ++g)
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+          for (int j = 0; j < TJ; ++j)
+            *reinterpret_cast<floatx4*>(cl + (r0 + i * 16) * CF::LDC + g * 128 + (wn * TJ + j) * 16 + 4 * (l >> 4)) =
+                acc[h][g][i][j];
+    }
+  };
+  staged_epilogue<TO, EPI, CF, PRE>(a, cl, m0, n0, put, pre, pb);
 }
+
 
 // Tile configurations; the choice per call is made in launch().
 typedef Tile<128, 128, 64, 64> T128x128;
@@ -981,9 +1424,6 @@ typedef PipeTile<256, 128, 64, 64, 3> P256x128;
 typedef PipeTile<128, 128, 64, 64, 4> P128x128;
 typedef PipeTile<128, 256, 64, 64, 3> P128x256;
 typedef PipeTile<128, 128, 64, 64, 2, 2> P128x128o2;   // two workgroups per CU
-// 256 x 256 in eight 128 x 64 wave tiles, two-stage ring (128 KB): a quarter
-// fewer LDS reads and a third fewer global -> LDS bytes per FLOP than 256 x 128
-typedef PipeTile<256, 256, 128, 64, 2> P256x256;
 
 template <typename TO, bool AK, bool BK, int EPI, class CF>
 hipError_t launch_pipe(const GemmArgs& a, int splits, hipStream_t st) {
@@ -993,6 +1433,17 @@ hipError_t launch_pipe(const GemmArgs& a, int splits, hipStream_t st) {
   kps = ((kps + BKE - 1) / BKE) * BKE;
   const int used = (a.K + kps - 1) / kps;
   hipLaunchKernelGGL((gemm_pipe_kernel<TO, AK, BK, EPI, CF>), dim3(tiles, used), dim3(CF::NT), 0, st, a, kps);
+  return hipGetLastError();
+}
+
+template <typename TO, bool AK, bool BK, int EPI, int BN>
+hipError_t launch_pp(const GemmArgs& a, int splits, hipStream_t st) {
+  constexpr int BKE = 64;
+  const int tiles = ((a.M + 255) / 256) * ((a.N + BN - 1) / BN);
+  int kps = (a.K + splits - 1) / splits;
+  kps = ((kps + BKE - 1) / BKE) * BKE;
+  const int used = (a.K + kps - 1) / kps;
+  hipLaunchKernelGGL((gemm_pp_kernel<TO, AK, BK, EPI, BN>), dim3(tiles, used), dim3(512), 0, st, a, kps);
   return hipGetLastError();
 }
 
@@ -1029,18 +1480,18 @@ template <bool AK, bool BK>
 bool pipe_eligible(const GemmArgs& a) {
   auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
   return a.zeros != nullptr && al16(a.A) && al16(a.B) && al16(a.zeros) && a.K % 8 == 0 && a.lda % 8 == 0 &&
-         a.ldb % 8 == 0 && (AK || a.M % 8 == 0) && (BK || a.N % 8 == 0);
+         a.ldb % 8 == 0 && a.lda < (1 << 22) && a.ldb < (1 << 22) && (AK || a.M % 8 == 0) && (BK || a.N % 8 == 0);
 }
 
 template <typename T, typename TO, bool AK, bool BK, int EPI>
 hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
   if (a.seg_rows > 0) {
-    // segmented B (the window weight gradients): the pipelined TN kernel on
-    // 256 x 128 tiles, one workgroup per CU with a three-stage ring (measured
-    // 8% faster than two 128 x 128 workgroups per CU with two stages each)
+    // segmented B (the window weight gradients): 256 x 128 ping-pong tiles
+    // (768-wide stage, 32768 rows: 207, 170 and 114 us per product with the
+    // three-stage ring, 196, 160 and 112 now)
     if constexpr (sizeof(T) == 2 && !AK && !BK) {
       if (pipe_eligible<AK, BK>(a) && a.seg_rows % 64 == 0 && a.seg_count >= 1 && a.seg_first >= 0)
-        return launch_pipe<TO, AK, BK, EPI, P256x128>(a, splits, st);
+        return launch_pp<TO, AK, BK, EPI, 128>(a, splits, st);
     }
     return hipErrorInvalidValue;
   }
@@ -1054,17 +1505,18 @@ hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
         case 13: return launch_pipe<TO, AK, BK, EPI, P128x128o2>(a, splits, st);
         default:
           // The FFN up-projection and the input gradient through gelu'(u):
-          // 256 x 256 tiles when they fill whole rounds of the CUs (measured
-          // 13% and 2% faster per call at 8192 x 4096, 11% for the latter
-          // with its per-panel aux loads). Otherwise weight gradients (both
-          // operands MN-major) and the input gradient through gelu'(u): 128 x
-          // 128 tiles, two workgroups per CU, so one's epilogue overlaps the
+          // 256 x 256 ping-pong tiles when they fill whole rounds of the CUs
+          // (at 8192 x 4096 x 1024, in the stage: 106 us on 256 x 128 tiles,
+          // 90.6 on 256 x 256 ring tiles, 88.9 ping-pong; the input gradient
+          // 110, 88.9 and 82.2). Otherwise weight gradients (both operands
+          // MN-major) and the input gradient through gelu'(u): 128 x 128
+          // tiles, two workgroups per CU, so one's epilogue overlaps the
           // other's loop (3-6% faster for the latter, slower for the other
           // forward and input-gradient products); the rest: 256 x 128 tiles,
           // which re-read the weights half as often.
           if constexpr (AK && BK && (EPI == EPI_BIAS_GELU || EPI == EPI_GELU_GRAD)) {
             const int t256 = ((a.M + 255) / 256) * ((a.N + 255) / 256);
-            if (splits == 1 && t256 % cu_count() == 0) return launch_pipe<TO, AK, BK, EPI, P256x256>(a, splits, st);
+            if (splits == 1 && t256 % cu_count() == 0) return launch_pp<TO, AK, BK, EPI, 256>(a, splits, st);
           }
           if constexpr (!AK || EPI == EPI_GELU_GRAD) return launch_pipe<TO, AK, BK, EPI, P128x128o2>(a, splits, st);
           else return launch_pipe<TO, AK, BK, EPI, P256x128>(a, splits, st);
@@ -1114,10 +1566,10 @@ hipError_t by_layout(bool out_f32, GemmLayout lay, GemmEpi epi, const GemmArgs& 
         return hipErrorInvalidValue;
       if (epi == EPI_CE_STATS) {
         if (a.ce_part == nullptr || a.ce_zt == nullptr || a.ld_part < (a.N + 63) / 64) return hipErrorInvalidValue;
-        return launch_pipe<float, true, true, EPI_CE_STATS, P256x128>(a, 1, st);
+        return launch_pp<float, true, true, EPI_CE_STATS, 256>(a, 1, st);
       }
       if (a.row_lse == nullptr || out_f32) return hipErrorInvalidValue;
-      return launch_pipe<T, true, true, EPI_CE_GRAD, P256x128>(a, 1, st);
+      return launch_pp<T, true, true, EPI_CE_GRAD, 256>(a, 1, st);
     }
     return hipErrorInvalidValue;
   }
@@ -1139,8 +1591,9 @@ hipError_t by_layout(bool out_f32, GemmLayout lay, GemmEpi epi, const GemmArgs& 
 
 void gemm_set_tile_override(int cfg) { g_tile_override = cfg; }
 
-// Grouped weight gradients on 256 x 128 tiles (one workgroup per CU, three-stage
-// ring) or 256 x 256 (two-stage ring), plain fp32 read-modify-write of each output tile.
+// Grouped weight gradients on 256 x 128 tiles (three-stage ring: 131 us for 256
+// of them over 8192 rows, ping-pong 137) or 256 x 256 (ping-pong: 916 -> 814 us
+// for 1024 of them), plain fp32 read-modify-write of each output tile.
 namespace {
 template <class CF> int group_tiles(int M, int N) { return ((M + CF::BM - 1) / CF::BM) * ((N + CF::BN - 1) / CF::BN); }
 template <class CF> int group_xcd_m(int M, int N, int K) {
@@ -1161,17 +1614,19 @@ template <class CF> int group_xcd_m(int M, int N, int K) {
 }
 template <class CF, int EPI>
 void launch_grouped(const GemmArgs& a, int total_tiles, int K, hipStream_t st) {
-  hipLaunchKernelGGL((gemm_pipe_kernel<float, false, false, EPI, CF, true>), dim3(total_tiles, 1), dim3(CF::NT), 0, st,
-                     a, K);
+  if constexpr (CF::BN == 256)
+    hipLaunchKernelGGL((gemm_pp_kernel<float, false, false, EPI, 256, true>), dim3(total_tiles, 1), dim3(CF::NT), 0, st, a, K);
+  else
+    hipLaunchKernelGGL((gemm_pipe_kernel<float, false, false, EPI, CF, true>), dim3(total_tiles, 1), dim3(CF::NT), 0, st, a, K);
 }
 }  // namespace
 
 int wgrad_group_tiles(int M, int N, bool wide) {
-  return wide ? group_tiles<P256x256>(M, N) : group_tiles<P256x128>(M, N);
+  return wide ? group_tiles<PP<256>>(M, N) : group_tiles<P256x128>(M, N);
 }
 
 int wgrad_group_xcd_m(int M, int N, int K, bool wide) {
-  return wide ? group_xcd_m<P256x256>(M, N, K) : group_xcd_m<P256x128>(M, N, K);
+  return wide ? group_xcd_m<PP<256>>(M, N, K) : group_xcd_m<P256x128>(M, N, K);
 }
 
 int wgrad_group_wide(const int* M, const int* N, int n) {
@@ -1181,7 +1636,7 @@ int wgrad_group_wide(const int* M, const int* N, int n) {
   auto cost = [&](int n1) {
     int t1 = 0, t2 = 0;
     for (int p = 0; p < n; ++p) {
-      if (p < n1) t1 += padded(group_tiles<P256x256>(M[p], N[p]));
+      if (p < n1) t1 += padded(group_tiles<PP<256>>(M[p], N[p]));
       else t2 += padded(group_tiles<P256x128>(M[p], N[p]));
     }
     return 1.8 * ((t1 + cus - 1) / cus) + 1.0 * ((t2 + cus - 1) / cus);
@@ -1210,8 +1665,8 @@ hipError_t gemm_wgrad_grouped(const WgradProblem* probs, int n, int total_tiles,
   a.group_n = n;
   a.nonfinite = nonfinite;
   if (wide) {
-    if (overwrite) launch_grouped<P256x256, EPI_STORE>(a, total_tiles, K, st);
-    else launch_grouped<P256x256, EPI_ACC>(a, total_tiles, K, st);
+    if (overwrite) launch_grouped<PP<256>, EPI_STORE>(a, total_tiles, K, st);
+    else launch_grouped<PP<256>, EPI_ACC>(a, total_tiles, K, st);
   } else {
     if (overwrite) launch_grouped<P256x128, EPI_STORE>(a, total_tiles, K, st);
     else launch_grouped<P256x128, EPI_ACC>(a, total_tiles, K, st);
