@@ -528,7 +528,7 @@ __device__ __forceinline__ void staged_out(const GemmArgs& a, const float* cl, i
       const float l = a.row_lse[m];
       const int y = a.row_tgt[m] - n;
 #pragma unroll
-      for (int j = 0; j < U; ++j) o[j] = a.alpha * (expf(o[j] - l) - (j == y ? 1.f : 0.f));
+      for (int j = 0; j < U; ++j) o[j] = a.alpha * (fast_exp(o[j] - l) - (j == y ? 1.f : 0.f));
     } else {
 #pragma unroll
       for (int j = 0; j < U; ++j) {
@@ -589,8 +589,8 @@ __device__ __forceinline__ void staged_out(const GemmArgs& a, const float* cl, i
 // Cross-entropy row statistics of a staged panel (EPI_CE_STATS): per row and
 // 64-column group, the maximum and the sum of exp(x - max) over the valid
 // columns, and the target's logit when the group holds it. Consecutive lanes
-// take consecutive rows; a full group is read starting at column r mod 64, so
-// the 64 lanes of a wavefront hit 64 distinct banks (row stride BN + 4).
+// take consecutive rows; at row stride BN + 4 floats the 16-byte reads of 16
+// lanes cover the 64 banks once.
 template <int BN, int PR, int NT>
 __device__ __forceinline__ void ce_stats_panel(const GemmArgs& a, const float* cl, int mb, int n0, int tid) {
   constexpr int LDC = BN + 4, G = BN / 64;
@@ -601,11 +601,22 @@ __device__ __forceinline__ void ce_stats_panel(const GemmArgs& a, const float* c
     if (m >= a.M || nb >= a.N) continue;
     const int nv = min(64, a.N - nb);
     const float* row = cl + r * LDC + 64 * g;
-    const int rot = nv == 64 ? r : 0;
-    float mx = -INFINITY;
-    for (int c = 0; c < nv; ++c) mx = fmaxf(mx, row[(c + rot) & 63]);
-    float sum = 0.f;
-    for (int c = 0; c < nv; ++c) sum += expf(row[(c + rot) & 63] - mx);
+    float mx = -INFINITY, sum = 0.f;
+    if (nv == 64) {
+      floatx4 v[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        v[c] = *reinterpret_cast<const floatx4*>(row + 4 * c);
+        mx = fmaxf(fmaxf(mx, fmaxf(v[c][0], v[c][1])), fmaxf(v[c][2], v[c][3]));
+      }
+#pragma unroll
+      for (int c = 0; c < 16; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum += fast_exp(v[c][j] - mx);
+    } else {
+      for (int c = 0; c < nv; ++c) mx = fmaxf(mx, row[c]);
+      for (int c = 0; c < nv; ++c) sum += fast_exp(row[c] - mx);
+    }
     const int64_t q = (int64_t)m * a.ld_part + nb / 64;
     *reinterpret_cast<float2*>(a.ce_part + 2 * q) = make_float2(mx, sum);
     const int y = a.row_tgt[m] - nb;
@@ -652,6 +663,7 @@ __device__ __forceinline__ void staged_epilogue(const GemmArgs& a, float* cl, in
         if (m < a.M && n < a.N) atomicAdd(C + (int64_t)m * a.ldc + n, cl[r * LDC + c]);
       }
     } else {
+      if constexpr (EPI == EPI_STORE_CE) ce_stats_panel<BN, PR, NT>(a, cl, mb, n0, tid);
       if constexpr (PANEL_AUX) staged_out<TO, EPI, BN, PR, NT, true>(a, cl, mb, n0, tid, csum, pre_p, pb);
       else staged_out<TO, EPI, BN, PR, NT, PRE>(a, cl, mb, n0, tid, csum, pre, pb);
     }
@@ -1471,16 +1483,22 @@ hipError_t launch_cf(const GemmArgs& a, int splits, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The pipelined kernel moves whole 16-byte chunks of 8 elements from global
-// memory to LDS, so every chunk must be aligned and lie wholly inside or wholly
-// outside the operand: 16-byte aligned bases, leading dimensions and K (and the
-// contiguous M or N of an MN-major operand) multiples of 8. Other calls take
-// the register-staged kernel, which masks partial vectors.
+// The pipelined kernels move whole 16-byte chunks of 8 elements from global
+// memory to LDS: bases and leading dimensions must be aligned to them. A chunk
+// of a K-major operand that straddles K must be zero past it in A (the other
+// operand's contracted rows are masked one by one): K a multiple of 8, or A
+// zero-padded and B MN-major; both MN-major: any K. A chunk of an MN-major
+// operand that straddles M or N only feeds outputs that are not stored, and
+// must exist: M (N) a multiple of 8, or a leading dimension that covers the
+// chunk. Other calls take the register-staged kernel, which masks partial
+// vectors.
 template <bool AK, bool BK>
 bool pipe_eligible(const GemmArgs& a) {
   auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  return a.zeros != nullptr && al16(a.A) && al16(a.B) && al16(a.zeros) && a.K % 8 == 0 && a.lda % 8 == 0 &&
-         a.ldb % 8 == 0 && a.lda < (1 << 22) && a.ldb < (1 << 22) && (AK || a.M % 8 == 0) && (BK || a.N % 8 == 0);
+  auto covers = [](int64_t ld, int n) { return n % 8 == 0 || ld >= (n + 7) / 8 * 8; };
+  const bool k_ok = a.K % 8 == 0 || (!AK && !BK) || (AK && !BK && a.a_zero_pad);
+  return a.zeros != nullptr && al16(a.A) && al16(a.B) && al16(a.zeros) && k_ok && a.lda % 8 == 0 && a.ldb % 8 == 0 &&
+         a.lda < (1 << 22) && a.ldb < (1 << 22) && (AK || covers(a.lda, a.M)) && (BK || covers(a.ldb, a.N));
 }
 
 template <typename T, typename TO, bool AK, bool BK, int EPI>
@@ -1518,6 +1536,11 @@ hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
             const int t256 = ((a.M + 255) / 256) * ((a.N + 255) / 256);
             if (splits == 1 && t256 % cu_count() == 0) return launch_pp<TO, AK, BK, EPI, 256>(a, splits, st);
           }
+          // An MN-major weight operand (the LM head's input gradient, K = V):
+          // 256 x 128 ping-pong tiles, whose partial last k-tile does not slow
+          // the others (8192 x 1024 x 50257: 1115 us on the register-staged
+          // kernel, 690 now).
+          if constexpr (AK && !BK && EPI == EPI_STORE) return launch_pp<TO, AK, BK, EPI, 128>(a, splits, st);
           if constexpr (!AK || EPI == EPI_GELU_GRAD) return launch_pipe<TO, AK, BK, EPI, P128x128o2>(a, splits, st);
           else return launch_pipe<TO, AK, BK, EPI, P256x128>(a, splits, st);
       }
@@ -1559,13 +1582,17 @@ hipError_t by_layout(bool out_f32, GemmLayout lay, GemmEpi epi, const GemmArgs& 
     return hipErrorInvalidValue;
   }
   if (splits != 1) return hipErrorInvalidValue;
-  if (epi == EPI_CE_STATS || epi == EPI_CE_GRAD) {
+  if (epi == EPI_CE_STATS || epi == EPI_STORE_CE || epi == EPI_CE_GRAD) {
     // pipelined bf16 kernel only; the statistics need 64-column groups
     if constexpr (sizeof(T) == 2) {
       if (lay != GEMM_NT || !pipe_eligible<true, true>(a) || a.row_tgt == nullptr || a.colsum != nullptr)
         return hipErrorInvalidValue;
-      if (epi == EPI_CE_STATS) {
+      // 256 x 256 ping-pong tiles (8192 x 50257 x 1024: 1120 us storing fp32 logits on 256 x 128
+      // ring tiles, 1015 with the statistics, which save a 953 us pass over the logits; without
+      // logits 1085 -> 750 and 1200 -> 880 us)
+      if (epi != EPI_CE_GRAD) {
         if (a.ce_part == nullptr || a.ce_zt == nullptr || a.ld_part < (a.N + 63) / 64) return hipErrorInvalidValue;
+        if (epi == EPI_STORE_CE) return launch_pp<float, true, true, EPI_STORE_CE, 256>(a, 1, st);
         return launch_pp<float, true, true, EPI_CE_STATS, 256>(a, 1, st);
       }
       if (a.row_lse == nullptr || out_f32) return hipErrorInvalidValue;
@@ -1655,7 +1682,7 @@ int wgrad_group_wide(const int* M, const int* N, int n) {
 
 hipError_t gemm_wgrad_grouped(const WgradProblem* probs, int n, int total_tiles, int K, const void* zeros,
                               bool overwrite, bool wide, int* nonfinite, hipStream_t st) {
-  if (probs == nullptr || n < 1 || total_tiles < 1 || K < 1 || K % 8 || zeros == nullptr ||
+  if (probs == nullptr || n < 1 || total_tiles < 1 || K < 1 || zeros == nullptr ||
       (reinterpret_cast<uintptr_t>(zeros) & 15))
     return hipErrorInvalidValue;
   GemmArgs a{};
@@ -1680,7 +1707,7 @@ int gemm_acc_splits(DType dt, int M, int N, int K) {
   // k-tiles each runs (about 2.3 TFLOP/s per CU, shared by its workgroups),
   // plus the fp32 read-modify-write or atomic adds of the epilogue (about
   // 2 ps per element and split).
-  const bool pipe = dt == DT_BF16 && K % 8 == 0 && M % 8 == 0 && N % 8 == 0;
+  const bool pipe = dt == DT_BF16 && N % 8 == 0;
   const int bm = pipe ? P128x128o2::BM : T128x128::BM, bn = pipe ? P128x128o2::BN : T128x128::BN;
   const int bk = pipe ? 64 : KVN * (dt == DT_BF16 ? 8 : 4);
   const int occ = pipe ? P128x128o2::OCC : 1;   // workgroups resident per CU
@@ -1699,6 +1726,30 @@ int gemm_acc_splits(DType dt, int M, int N, int K) {
     }
   }
   return best;
+}
+
+hipError_t gemm_wgrad(DType dt, const GemmArgs& a, hipStream_t st) {
+  if (a.M <= 0 || a.N <= 0 || a.K <= 0 || a.colsum != nullptr || a.seg_rows > 0) return hipErrorInvalidValue;
+  GemmArgs r = a;
+  // At least one whole round of 256 x 256 tiles: that many whole rounds on the
+  // ping-pong kernel and the remaining rows split over K, since a last partial
+  // round would leave most CUs idle for as long as a full one. The 50257 x 1024
+  // LM head over 8192 rows: 1453 us on the register-staged 128 x 128 kernel,
+  // 625 (3 rounds) + 50 us now.
+  if (dt == DT_BF16 && pipe_eligible<false, false>(a)) {
+    const int cus = cu_count(), tn = (a.N + 255) / 256, tm = a.M / 256;
+    const int rows_t = tn <= cus ? tm * tn / cus * cus / tn : 0;   // row tiles of the whole rounds
+    if (rows_t > 0) {
+      r.M = rows_t * 256;
+      const hipError_t e = launch_pp<float, false, false, EPI_ACC, 256>(r, 1, st);
+      if (e != hipSuccess || r.M == a.M) return e;
+      r.A = reinterpret_cast<const bf16*>(a.A) + r.M;
+      r.C = reinterpret_cast<float*>(a.C) + (int64_t)r.M * a.ldc;
+      r.M = a.M - rows_t * 256;
+    }
+  }
+  const int splits = gemm_acc_splits(dt, r.M, r.N, r.K);
+  return gemm(dt, true, GEMM_TN, splits > 1 ? EPI_ATOMIC : EPI_ACC, r, splits, st);
 }
 
 hipError_t gemm(DType dt, bool out_f32, GemmLayout lay, GemmEpi epi, const GemmArgs& a, int splits,

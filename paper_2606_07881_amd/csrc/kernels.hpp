@@ -35,9 +35,10 @@ enum GemmLayout { GEMM_NT = 0, GEMM_NN = 1, GEMM_TN = 2 };
 //   EPI_CE_STATS   nothing stored in C; per row m and 64-column group g (columns
 //                  64g .. 64g+63 below N): ce_part[2 (m ld_part + g) + {0, 1}] =
 //                  {max, sum exp(acc - max)}; ce_zt[m] = acc at column row_tgt[m]
+//   EPI_STORE_CE   C = acc (fp32) and the statistics of EPI_CE_STATS
 //   EPI_CE_GRAD    C = alpha * (exp(acc - row_lse[m]) - [n == row_tgt[m]])  (bf16)
 enum GemmEpi { EPI_STORE = 0, EPI_BIAS, EPI_BIAS_RES, EPI_BIAS_GELU, EPI_GELU_GRAD, EPI_ACC, EPI_ATOMIC, EPI_CE_STATS,
-               EPI_CE_GRAD };
+               EPI_STORE_CE, EPI_CE_GRAD };
 
 // Grouped weight gradients (bf16, one launch): problem p adds
 // C_p[M_p, N_p] (fp32, row stride N_p) += A_p^T B_p over K contracted rows, with
@@ -82,6 +83,7 @@ struct GemmArgs {
   const WgradProblem* group = nullptr;
   int group_n = 0;
   int* nonfinite = nullptr;   // fp32 EPI_ACC / EPI_STORE: set to 1 if an element written is not finite
+  bool a_zero_pad = false;    // K-major A: elements K .. roundup(K, 8) - 1 of every row exist and are zero
 };
 // bf16 operands: K-major vectors that straddle K read the memory just past K,
 // which must hold zeros (true when K % 8 == 0, or for zero-padded rows).
@@ -104,6 +106,10 @@ int wgrad_group_wide(const int* M, const int* N, int n);
 hipError_t gemm_wgrad_grouped(const WgradProblem* probs, int n, int total_tiles, int K, const void* zeros,
                               bool overwrite, bool wide, int* nonfinite, hipStream_t st);
 
+// Cf32 += A^T B (GEMM_TN, one problem): large products as whole rounds of 256 x 256
+// tiles (plain read-modify-write) plus the remaining rows, others split over K
+// (gemm_acc_splits; fp32 atomics when split).
+hipError_t gemm_wgrad(DType dt, const GemmArgs& a, hipStream_t st);
 // dtype: element type of A, B, aux and of C/C2 unless out_f32 (then C is float).
 // splits > 1 is only valid with EPI_ATOMIC.
 hipError_t gemm(DType dt, bool out_f32, GemmLayout lay, GemmEpi epi, const GemmArgs& a, int splits, hipStream_t st);

@@ -347,7 +347,7 @@ struct Layout {
   // window), and the pre-dropout branch output in the forward
   bool dropout = false;
   size_t w_dyu = 0, w_dx1u = 0, w_g2 = 0, w_zdrop = 0;
-  // fused LM head: no logits per slot; (max, sum) per row and 64 columns, target logits
+  // fused LM head: no logits per slot. bf16: (max, sum) per row and 64 columns, target logits
   bool fused_head = false;
   int ngroups = 0;
   size_t w_cepart = 0, w_zt = 0;
@@ -457,7 +457,7 @@ Layout make_layout(const paci_shapes& s, int K, int delay, const ParamTable& p) 
   L.slot_bytes = (sl.off + 255) & ~(size_t)255;
   L.recompute = s.recompute != 0;
   L.window = s.window != 0;   // validate_shapes admits it only where the windowed kernels apply
-  L.wdefer = !L.window && s.dtype == PACI_BF16 && T % 8 == 0 && d % 8 == 0 && f % 8 == 0;
+  L.wdefer = !L.window && s.dtype == PACI_BF16 && d % 8 == 0 && f % 8 == 0;
   L.n_slots = L.window ? K + delay : delay + 1;
   if (L.recompute) {
     Bump c;
@@ -518,7 +518,7 @@ Layout make_layout(const paci_shapes& s, int K, int delay, const ParamTable& p) 
     part = std::max(part, paci::ce_part_floats((int)T));
     L.w_dz = a.take(esz * T * L.ldz);
     L.w_dnf = a.take(esz * T * d);
-    if (L.fused_head) {
+    if (s.dtype == PACI_BF16) {
       L.ngroups = (int)(L.ldz / 64);
       L.w_cepart = a.take(8 * T * (int64_t)L.ngroups);
       L.w_zt = a.take(4 * T);
@@ -694,6 +694,7 @@ int linear_dgrad(paci_stage* h, const void* dY, int64_t ldy, int64_t w_off, int 
   paci::GemmArgs a{dY, ldy, tr ? h->WT(w_off) : h->W(w_off), tr ? K : N, M, N, K, C, N, nullptr, aux, N, nullptr,
                    h->arena + h->L.zeros};
   if (colsum_off >= 0) a.colsum = h->g(colsum_off);
+  a.a_zero_pad = !block;   // the LM head's dz: zero columns up to its stride, a multiple of 64
   return run(h, F_GEMM_DGRAD, 2.0 * M * N * K,
              [&] { return paci::gemm(h->dt, false, tr ? paci::GEMM_NT : paci::GEMM_NN, epi, a, 1, h->st); });
 }
@@ -717,11 +718,8 @@ int refresh_wT(paci_stage* h) {
 // G[out, in] += dY[T, out]^T X[T, in]
 int linear_wgrad(paci_stage* h, const void* dY, int64_t ldy, const void* X, int64_t ldx, int out, int in, int T,
                  int64_t g_off) {
-  const int splits = paci::gemm_acc_splits(h->dt, out, in, T);
   paci::GemmArgs a{dY, ldy, X, ldx, out, in, T, h->g(g_off), in, nullptr, nullptr, 0, nullptr, h->arena + h->L.zeros};
-  const paci::GemmEpi epi = splits > 1 ? paci::EPI_ATOMIC : paci::EPI_ACC;
-  return run(h, F_GEMM_WGRAD, 2.0 * out * in * T,
-             [&] { return paci::gemm(h->dt, true, paci::GEMM_TN, epi, a, splits, h->st); });
+  return run(h, F_GEMM_WGRAD, 2.0 * out * in * T, [&] { return paci::gemm_wgrad(h->dt, a, h->st); });
 }
 
 int bias_grad(paci_stage* h, const void* Y, int64_t ld, int rows, int ncols, int64_t g_off) {
@@ -1017,30 +1015,30 @@ int stage_forward_into(paci_stage* h, char* A, const void* in, void* x0_copy, co
   float* meanf = reinterpret_cast<float*>(A + L.s_meanf);
   float* rstdf = reinterpret_cast<float*>(A + L.s_rstdf);
   TRY(ln_fwd(h, A + L.s_y, A + L.s_nf, meanf, rstdf, h->p.lnf_g, h->p.lnf_b, nullptr));
-  if (L.fused_head) {
-    // logits reduced to (max, sum) per 64 columns inside the product, then per row
-    paci::GemmArgs a{A + L.s_nf, d, h->W(h->p.w_lm), d, T, s.vocab, d, nullptr, 0, nullptr, nullptr, 0, nullptr,
-                     h->arena + L.zeros};
+  float* lse = reinterpret_cast<float*>(A + L.s_lse_ce);
+  float* part = reinterpret_cast<float*>(h->ws(L.w_part));
+  float* z = L.fused_head ? nullptr : reinterpret_cast<float*>(A + L.s_z);
+  paci::GemmArgs a{A + L.s_nf, d, h->W(h->p.w_lm), d, T, s.vocab, d, z, L.ldz, nullptr, nullptr, 0, nullptr,
+                   h->arena + L.zeros};
+  if (h->dt == paci::DT_BF16) {
+    // logits reduced to (max, sum) per 64 columns inside the product (and stored unless the head is
+    // fused), then per row: no pass over the logits
     a.row_tgt = tgt;
     a.ce_part = reinterpret_cast<float*>(h->ws(L.w_cepart));
     a.ld_part = L.ngroups;
     a.ce_zt = reinterpret_cast<float*>(h->ws(L.w_zt));
+    const paci::GemmEpi epi = L.fused_head ? paci::EPI_CE_STATS : paci::EPI_STORE_CE;
     TRY(run(h, F_GEMM_FWD, 2.0 * T * s.vocab * d,
-            [&] { return paci::gemm(h->dt, true, paci::GEMM_NT, paci::EPI_CE_STATS, a, 1, h->st); }));
+            [&] { return paci::gemm(h->dt, true, paci::GEMM_NT, epi, a, 1, h->st); }));
     return run(h, F_CE, 8.0 * T * L.ngroups + 16.0 * T, [&] {
-      return paci::ce_combine(a.ce_part, L.ngroups, L.ngroups, a.ce_zt, tgt, s.vocab,
-                              reinterpret_cast<float*>(A + L.s_lse_ce), reinterpret_cast<float*>(out),
-                              reinterpret_cast<float*>(h->ws(L.w_part)), T, h->st);
+      return paci::ce_combine(a.ce_part, L.ngroups, L.ngroups, a.ce_zt, tgt, s.vocab, lse,
+                              reinterpret_cast<float*>(out), part, T, h->st);
     });
   }
-  float* z = reinterpret_cast<float*>(A + L.s_z);
-  paci::GemmArgs a{A + L.s_nf, d, h->W(h->p.w_lm), d, T, s.vocab, d, z, L.ldz, nullptr, nullptr, 0, nullptr,
-                   h->arena + L.zeros};
   TRY(run(h, F_GEMM_FWD, 2.0 * T * s.vocab * d,
           [&] { return paci::gemm(h->dt, true, paci::GEMM_NT, paci::EPI_STORE, a, 1, h->st); }));
   return run(h, F_CE, 4.0 * T * s.vocab, [&] {
-    return paci::ce_fwd(z, L.ldz, tgt, reinterpret_cast<float*>(A + L.s_lse_ce), reinterpret_cast<float*>(out),
-                        reinterpret_cast<float*>(h->ws(L.w_part)), T, s.vocab, h->st);
+    return paci::ce_fwd(z, L.ldz, tgt, lse, reinterpret_cast<float*>(out), part, T, s.vocab, h->st);
   });
 }
 

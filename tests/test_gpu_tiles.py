@@ -28,11 +28,28 @@ def test_pingpong_kmajor(binding, d):  # noqa: F811
 
 
 # the same tiles with both operands MN-major (grouped weight gradients): 1 to 4
-# k-tiles over T
-@pytest.mark.parametrize("T", [40, 64, 72, 128, 200])
-def test_pingpong_grouped(binding, T):  # noqa: F811
-    _check(binding, small_cfg("tall_bf16", d_model=1024, n_heads=16, head_dim=64, d_ff=4096, seq=T // 2,
-                              micro_batch=2))
+# k-tiles over T, T a multiple of 8 or odd
+@pytest.mark.parametrize("seq,mu", [(20, 2), (64, 1), (36, 2), (25, 3), (64, 2), (67, 3)])
+def test_pingpong_grouped(binding, seq, mu):  # noqa: F811
+    _check(binding, small_cfg("tall_bf16", d_model=1024, n_heads=16, head_dim=64, d_ff=4096, seq=seq, micro_batch=mu))
+
+
+# grouped weight gradients on the ring kernel's tiles over an odd T
+@pytest.mark.parametrize("seq,mu", [(33, 1), (33, 3), (101, 5)])
+def test_grouped_odd_tokens(binding, seq, mu):  # noqa: F811
+    _check(binding, small_cfg("ragged_bf16", seq=seq, micro_batch=mu))
+
+
+# LM head on the pipelined kernels at vocabularies that are not multiples of 8:
+# input gradient over K = V with a partial last chunk and k-tile; weight
+# gradient with and without a whole round of 256 x 256 tiles (64 row tiles at
+# d 1024) and a remainder; logits kept and not kept
+@pytest.mark.parametrize("fused", [0, 1])
+@pytest.mark.parametrize("V,d,seq,mu", [(63, 128, 72, 2), (257, 64, 33, 1), (1003, 128, 100, 2), (16384, 1024, 36, 2),
+                                        (16391, 1024, 25, 3), (17001, 1024, 36, 2)])
+def test_lm_head(binding, V, d, seq, mu, fused):  # noqa: F811
+    _check(binding, small_cfg("last_bf16", vocab=V, d_model=d, n_heads=d // 64, head_dim=64, d_ff=256, seq=seq,
+                              micro_batch=mu, fused_head=fused))
 
 
 # 256 x 128 ping-pong tiles over segments (window products): 1 to 6 k-tiles, one micro-batch
