@@ -149,7 +149,7 @@ template <int ROWS> __device__ __forceinline__ int trt_elem(int k, int r) {
   return k * ROWS + (((r >> 3) ^ trt_swz<ROWS>(k)) << 3) + (r & 7);
 }
 typedef short i16x4 __attribute__((ext_vector_type(4)));
-// The same read from a precomputed address: off = lds_frag_tr_off<ROWS>(row0)
+// The read from a precomputed address: off = lds_frag_tr_off<ROWS>(row0)
 // is this lane's byte offset within the tile for step 0, and the tile's LDS
 // byte address is added per read. Lines k0 + 4 and k0 + 32 s keep the swizzle
 // of line k0 (k0 = 8 g + 0..3 leaves bits 0, 1 and 3 unchanged by those
@@ -167,20 +167,6 @@ template <int ROWS> __device__ __forceinline__ u32x4 lds_frag_tr_at(uint32_t add
   const u32x2 a = __builtin_bit_cast(u32x2, lo), b = __builtin_bit_cast(u32x2, hi);
   return u32x4{a[0], a[1], b[0], b[1]};
 }
-template <int ROWS> __device__ __forceinline__ u32x4 lds_frag_tr(const u32x4* tile, int s, int row0) {
-  const int l = lane_id();
-  const int g = l >> 4, c = l & 15;
-  const bf16* base = reinterpret_cast<const bf16*>(tile);
-  const int r = row0 + 4 * (c & 3);
-  const int k0 = s * 32 + 8 * g + (c >> 2);
-  const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) i16x4*)(base + trt_elem<ROWS>(k0, r)));
-  const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) i16x4*)(base + trt_elem<ROWS>(k0 + 4, r)));
-  const u32x2 a = __builtin_bit_cast(u32x2, lo), b = __builtin_bit_cast(u32x2, hi);
-  return u32x4{a[0], a[1], b[0], b[1]};
-}
-
 // ---- wave reductions ---------------------------------------------------------------------
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

@@ -1,16 +1,16 @@
 // Matrix-core GEMM for the stage's linear layers (forward, input gradient and
 // weight gradient with fused fp32 accumulation), gfx950.
 //
-// Work decomposition: one 256-thread workgroup (4 wavefronts, 2 x 2) per
-// 128 x 128 output tile; each wavefront owns a 64 x 64 sub-tile = 4 x 4 MFMA
-// 16 x 16 tiles. The contracted dimension advances in 8-vector slices (64 bf16 or
-// 32 fp32 elements), double-buffered in LDS: the global loads of slice k+1 are
-// in flight while slice k is multiplied. Operands stored contracted-major
-// (K-major) are copied as 16-byte vectors and read as one 16-byte fragment.
-// For bf16, operands stored the other way (MN-major: the weight in dX = dY W,
-// both activations in dW = dY^T X) are also copied as 16-byte vectors, into a
-// [k][rows] layout read with the gfx950 LDS transpose instruction. fp32
-// MN-major operands are transposed in registers (4 x 4 blocks).
+// bf16: the ring kernel (gemm_pipe_kernel, 64 x 64 to 256 x 128 tiles) and the
+// ping-pong kernel (gemm_pp_kernel, 256 x 256 and 256 x 128), both with
+// direct-to-LDS loads. fp32 (gemm_kernel): one 256-thread workgroup (4
+// wavefronts, 2 x 2) per 128 x 128, 64 x 64 or 32 x 32 output tile of 16 x 16
+// MFMA tiles; the contracted dimension advances in 32-element slices,
+// double-buffered in LDS, the global loads of slice k+1 in flight while slice k
+// is multiplied. Operands stored contracted-major (K-major) are copied as
+// 16-byte vectors and read as one 16-byte fragment; operands stored the other
+// way (MN-major: the weight in dX = dY W, both activations in dW = dY^T X) are
+// transposed in registers (4 x 4 blocks).
 //
 // Tile order is XCD-aware: workgroup w runs on XCD w % 8, so each XCD gets a
 // contiguous range of tiles, walked in groups of 8 tile-rows to keep A and B
@@ -33,17 +33,16 @@ struct Tile {
   static constexpr int NT = 64 * WAVES;
 };
 
-// Register-staged tile loader (global -> registers -> LDS).
-// K-major operands and MN-major bf16 operands are copied as 16-byte vectors
-// (MN-major bf16 into the [k][ROWS] transpose-read layout); MN-major fp32
-// operands are loaded as 4 x 4 blocks and transposed in registers.
+// Register-staged tile loader (global -> registers -> LDS), fp32. K-major
+// operands are copied as 16-byte vectors, MN-major ones loaded as 4 x 4 blocks
+// and transposed in registers.
 template <typename T, int ROWS, bool KMAJ, int NT>
 struct TileLoader {
+  static_assert(sizeof(T) == 4, "bf16 products take the direct-to-LDS kernels");
   static constexpr int V = Vec<T>::V;
-  static constexpr bool TR = !KMAJ && sizeof(T) == 2;   // transpose-read layout
-  static constexpr int ITEMS = (KMAJ || TR) ? ROWS * KVN : (ROWS / V) * KVN;
+  static constexpr int ITEMS = KMAJ ? ROWS * KVN : (ROWS / V) * KVN;
   static constexpr int PT = (ITEMS + NT - 1) / NT;
-  static constexpr int NV = (KMAJ || TR) ? 1 : V;
+  static constexpr int NV = KMAJ ? 1 : V;
   u32x4 r[PT][NV];
 
   // rows [row0, row0+ROWS) of `rows_total`; contracted [k0, k0 + 8V) of k_end.
@@ -60,16 +59,6 @@ struct TileLoader {
         if (row < rows_total && k < k_end) {
           v = ld16(src + (int64_t)row * ld + k);
           if (k + V > k_end) v = vmask_tail<T>(v, k_end - k);
-        }
-        r[p][0] = v;
-      } else if (TR) {
-        constexpr int CPL = ROWS / V;             // 16-byte chunks per contracted line
-        const int c = it % CPL, kk = it / CPL;
-        const int k = k0 + kk, rb = row0 + c * V;
-        u32x4 v = {0, 0, 0, 0};
-        if (k < k_end && rb < rows_total) {
-          v = ld16(src + (int64_t)k * ld + rb);
-          if (rb + V > rows_total) v = vmask_tail<T>(v, rows_total - rb);
         }
         r[p][0] = v;
       } else {
@@ -97,10 +86,6 @@ struct TileLoader {
       if (KMAJ) {
         const int kv = it % KVN, rr = it / KVN;
         tile[lds_slot<ROWS>(kv, rr)] = r[p][0];
-      } else if (TR) {
-        constexpr int CPL = ROWS / V;
-        const int c = it % CPL, kk = it / CPL;
-        st16(reinterpret_cast<bf16*>(tile) + trt_elem<ROWS>(kk, c * V), r[p][0]);
       } else {
         const int kv = it % KVN, rr = it / KVN;
         u32x4 out[V];
@@ -113,7 +98,6 @@ struct TileLoader {
 
   // operand fragment of MFMA step s for the 16 rows starting at row0
   __device__ __forceinline__ static u32x4 frag(const u32x4* tile, int s, int row0) {
-    if (TR) return lds_frag_tr<ROWS>(tile, s, row0);
     return lds_frag<ROWS>(tile, s, row0);
   }
 };
@@ -1429,13 +1413,15 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_kernel(GemmArgs a, int k_per_s
 
 // Tile configurations; the choice per call is made in launch().
 typedef Tile<128, 128, 64, 64> T128x128;
-
-int g_tile_override = -1;  // testing hook: force one configuration
+typedef Tile<64, 64, 32, 32> T64x64;
+typedef Tile<32, 32, 16, 16> T32x32;
 
 typedef PipeTile<256, 128, 64, 64, 3> P256x128;
-typedef PipeTile<128, 128, 64, 64, 4> P128x128;
-typedef PipeTile<128, 256, 64, 64, 3> P128x256;
 typedef PipeTile<128, 128, 64, 64, 2, 2> P128x128o2;   // two workgroups per CU
+// grids that leave CUs idle on the tiles above
+typedef PipeTile<128, 128, 32, 64, 4, 2> P128x128w8;
+typedef PipeTile<128, 64, 32, 32, 4, 2> P128x64;
+typedef PipeTile<64, 64, 32, 32, 4, 2> P64x64;
 
 template <typename TO, bool AK, bool BK, int EPI, class CF>
 hipError_t launch_pipe(const GemmArgs& a, int splits, hipStream_t st) {
@@ -1501,6 +1487,17 @@ bool pipe_eligible(const GemmArgs& a) {
          a.lda < (1 << 22) && a.ldb < (1 << 22) && (AK || covers(a.lda, a.M)) && (BK || covers(a.ldb, a.N));
 }
 
+// fp32 products: the largest tile edge that still gives two workgroups per CU,
+// else the smallest. A 256 x 128 product over 512 runs two 128 x 128 tiles on
+// the whole chip, or 32 of 32 x 32: 33 -> 8.4 us a launch over its calls with
+// K 128 and 512 (matrix work is 2.4, 0.7 and 0.45 us per 32-deep k-tile at 128,
+// 64 and 32, the last two bound by the latency of the loads).
+int f32_tile(int M, int N, int splits) {
+  for (int e = 128; e > 32; e /= 2)
+    if ((int64_t)((M + e - 1) / e) * ((N + e - 1) / e) * splits >= 2 * cu_count()) return e;
+  return 32;
+}
+
 template <typename T, typename TO, bool AK, bool BK, int EPI>
 hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
   if (a.seg_rows > 0) {
@@ -1515,38 +1512,55 @@ hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
   }
   if constexpr (sizeof(T) == 2) {
     if (pipe_eligible<AK, BK>(a)) {
-      switch (g_tile_override) {
-        case 0: break;  // register-staged kernel, for comparison
-        case 11: return launch_pipe<TO, AK, BK, EPI, P128x128>(a, splits, st);
-        case 12: return launch_pipe<TO, AK, BK, EPI, P128x256>(a, splits, st);
-        case 10: return launch_pipe<TO, AK, BK, EPI, P256x128>(a, splits, st);
-        case 13: return launch_pipe<TO, AK, BK, EPI, P128x128o2>(a, splits, st);
-        default:
-          // The FFN up-projection and the input gradient through gelu'(u):
-          // 256 x 256 ping-pong tiles when they fill whole rounds of the CUs
-          // (at 8192 x 4096 x 1024, in the stage: 106 us on 256 x 128 tiles,
-          // 90.6 on 256 x 256 ring tiles, 88.9 ping-pong; the input gradient
-          // 110, 88.9 and 82.2). Otherwise weight gradients (both operands
-          // MN-major) and the input gradient through gelu'(u): 128 x 128
-          // tiles, two workgroups per CU, so one's epilogue overlaps the
-          // other's loop (3-6% faster for the latter, slower for the other
-          // forward and input-gradient products); the rest: 256 x 128 tiles,
-          // which re-read the weights half as often.
-          if constexpr (AK && BK && (EPI == EPI_BIAS_GELU || EPI == EPI_GELU_GRAD)) {
-            const int t256 = ((a.M + 255) / 256) * ((a.N + 255) / 256);
-            if (splits == 1 && t256 % cu_count() == 0) return launch_pp<TO, AK, BK, EPI, 256>(a, splits, st);
-          }
-          // An MN-major weight operand (the LM head's input gradient, K = V):
-          // 256 x 128 ping-pong tiles, whose partial last k-tile does not slow
-          // the others (8192 x 1024 x 50257: 1115 us on the register-staged
-          // kernel, 690 now).
-          if constexpr (AK && !BK && EPI == EPI_STORE) return launch_pp<TO, AK, BK, EPI, 128>(a, splits, st);
-          if constexpr (!AK || EPI == EPI_GELU_GRAD) return launch_pipe<TO, AK, BK, EPI, P128x128o2>(a, splits, st);
-          else return launch_pipe<TO, AK, BK, EPI, P256x128>(a, splits, st);
+      // Grids that leave CUs idle: the largest tiles that still fit one round. A
+      // k-tile takes about 0.2 us on 64 x 64 tiles, 0.24 on 128 x 64, 0.36 on
+      // 128 x 128 and 0.6-0.8 on 256 x 128, so below one round of tiles the
+      // smaller ones win (128 x 768 x 3072: 34.1 us on 256 x 128, 12.8 on 64 x
+      // 64; 2048 x 768 x 3072: 36.9, 21.9 on 384 of 64 x 64, 18.3 on 192 of 128
+      // x 64; 4096 x 1024 x 4096: 48.8, 54.4, 49.1, 38.5 on 256 of 128 x 128),
+      // above it the larger ones, which re-read the operands less.
+      if constexpr (AK && BK && sizeof(TO) == 2) {
+        const int64_t cus = cu_count();
+        auto tiles = [&](int bm, int bn) { return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
+        if (splits == 1) {
+          if (tiles(64, 64) <= cus) return launch_pipe<TO, AK, BK, EPI, P64x64>(a, splits, st);
+          if (tiles(128, 64) <= cus) return launch_pipe<TO, AK, BK, EPI, P128x64>(a, splits, st);
+          if (tiles(128, 128) <= cus) return launch_pipe<TO, AK, BK, EPI, P128x128w8>(a, splits, st);
+        }
       }
+      // The FFN up-projection and the input gradient through gelu'(u):
+      // 256 x 256 ping-pong tiles when they fill whole rounds of the CUs
+      // (at 8192 x 4096 x 1024, in the stage: 106 us on 256 x 128 tiles,
+      // 90.6 on 256 x 256 ring tiles, 88.9 ping-pong; the input gradient
+      // 110, 88.9 and 82.2). Otherwise weight gradients (both operands
+      // MN-major) and the input gradient through gelu'(u): 128 x 128
+      // tiles, two workgroups per CU, so one's epilogue overlaps the
+      // other's loop (3-6% faster for the latter, slower for the other
+      // forward and input-gradient products); the rest: 256 x 128 tiles,
+      // which re-read the weights half as often.
+      if constexpr (AK && BK && (EPI == EPI_BIAS_GELU || EPI == EPI_GELU_GRAD)) {
+        const int t256 = ((a.M + 255) / 256) * ((a.N + 255) / 256);
+        if (splits == 1 && t256 % cu_count() == 0) return launch_pp<TO, AK, BK, EPI, 256>(a, splits, st);
+      }
+      // An MN-major weight operand (the LM head's input gradient, K = V):
+      // 256 x 128 ping-pong tiles, whose partial last k-tile does not slow
+      // the others (8192 x 1024 x 50257: 1115 us on the register-staged
+      // kernel, 690 now).
+      if constexpr (AK && !BK && EPI == EPI_STORE) return launch_pp<TO, AK, BK, EPI, 128>(a, splits, st);
+      if constexpr (!AK || EPI == EPI_GELU_GRAD) return launch_pipe<TO, AK, BK, EPI, P128x128o2>(a, splits, st);
+      else return launch_pipe<TO, AK, BK, EPI, P256x128>(a, splits, st);
     }
   }
-  hipError_t e = launch_cf<T, TO, AK, BK, EPI, T128x128>(a, splits, st);
+  hipError_t e;
+  if constexpr (sizeof(T) == 4) {
+    switch (f32_tile(a.M, a.N, splits)) {
+      case 32: e = launch_cf<T, TO, AK, BK, EPI, T32x32>(a, splits, st); break;
+      case 64: e = launch_cf<T, TO, AK, BK, EPI, T64x64>(a, splits, st); break;
+      default: e = launch_cf<T, TO, AK, BK, EPI, T128x128>(a, splits, st); break;
+    }
+  } else {
+    return hipErrorInvalidValue;   // every bf16 operand of a stage is aligned (d and f multiples of 32)
+  }
   if constexpr (EPI != EPI_ATOMIC && EPI != EPI_ACC) {
     // the register-staged epilogue has no column sums: one pass over the output
     if (e == hipSuccess && a.colsum != nullptr)
@@ -1616,12 +1630,19 @@ hipError_t by_layout(bool out_f32, GemmLayout lay, GemmEpi epi, const GemmArgs& 
 
 }  // namespace
 
-void gemm_set_tile_override(int cfg) { g_tile_override = cfg; }
-
 // Grouped weight gradients on 256 x 128 tiles (three-stage ring: 131 us for 256
 // of them over 8192 rows, ping-pong 137) or 256 x 256 (ping-pong: 916 -> 814 us
 // for 1024 of them), plain fp32 read-modify-write of each output tile.
 namespace {
+// f(CF{}) for the configuration of a tile shape
+template <class F> auto with_tile(WgradTile t, F&& f) {
+  switch (t) {
+    case WG_256x256: return f(PP<256>{});
+    case WG_128x128: return f(P128x128w8{});
+    case WG_64x64: return f(P64x64{});
+    default: return f(P256x128{});
+  }
+}
 template <class CF> int group_tiles(int M, int N) { return ((M + CF::BM - 1) / CF::BM) * ((N + CF::BN - 1) / CF::BN); }
 template <class CF> int group_xcd_m(int M, int N, int K) {
   const int tm = (M + CF::BM - 1) / CF::BM, tn = (N + CF::BN - 1) / CF::BN;
@@ -1648,23 +1669,34 @@ void launch_grouped(const GemmArgs& a, int total_tiles, int K, hipStream_t st) {
 }
 }  // namespace
 
-int wgrad_group_tiles(int M, int N, bool wide) {
-  return wide ? group_tiles<PP<256>>(M, N) : group_tiles<P256x128>(M, N);
+int wgrad_group_tiles(int M, int N, WgradTile tile) {
+  return with_tile(tile, [&](auto cf) { return group_tiles<decltype(cf)>(M, N); });
 }
 
-int wgrad_group_xcd_m(int M, int N, int K, bool wide) {
-  return wide ? group_xcd_m<PP<256>>(M, N, K) : group_xcd_m<P256x128>(M, N, K);
+int wgrad_group_xcd_m(int M, int N, int K, WgradTile tile) {
+  return with_tile(tile, [&](auto cf) { return group_xcd_m<decltype(cf)>(M, N, K); });
 }
 
-int wgrad_group_wide(const int* M, const int* N, int n) {
+int wgrad_group_split(const int* M, const int* N, int n, WgradTile* rest) {
   const int cus = cu_count();
   auto padded = [](int t) { return (t + 7) / 8 * 8; };
-  // cost in rounds of narrow tiles; n1 = 0 is the single narrow launch
+  auto total = [&](WgradTile t) {
+    int64_t sum = 0;
+    for (int p = 0; p < n; ++p) sum += padded(wgrad_group_tiles(M[p], N[p], t));
+    return sum;
+  };
+  // few tiles: smaller ones, so that more CUs share the work (a k-tile takes
+  // about 0.2 us on 64 x 64 tiles, 0.36 on 128 x 128 and 0.6-0.8 on 256 x 128)
+  *rest = WG_256x128;
+  if (total(WG_64x64) <= 2 * cus) *rest = WG_64x64;
+  else if (total(WG_128x128) <= cus) *rest = WG_128x128;
+  if (*rest != WG_256x128) return 0;
+  // cost in rounds of 256 x 128 tiles; n1 = 0 is the single launch
   auto cost = [&](int n1) {
     int t1 = 0, t2 = 0;
     for (int p = 0; p < n; ++p) {
-      if (p < n1) t1 += padded(group_tiles<PP<256>>(M[p], N[p]));
-      else t2 += padded(group_tiles<P256x128>(M[p], N[p]));
+      if (p < n1) t1 += padded(wgrad_group_tiles(M[p], N[p], WG_256x256));
+      else t2 += padded(wgrad_group_tiles(M[p], N[p], WG_256x128));
     }
     return 1.8 * ((t1 + cus - 1) / cus) + 1.0 * ((t2 + cus - 1) / cus);
   };
@@ -1681,7 +1713,7 @@ int wgrad_group_wide(const int* M, const int* N, int n) {
 }
 
 hipError_t gemm_wgrad_grouped(const WgradProblem* probs, int n, int total_tiles, int K, const void* zeros,
-                              bool overwrite, bool wide, int* nonfinite, hipStream_t st) {
+                              bool overwrite, WgradTile tile, int* nonfinite, hipStream_t st) {
   if (probs == nullptr || n < 1 || total_tiles < 1 || K < 1 || zeros == nullptr ||
       (reinterpret_cast<uintptr_t>(zeros) & 15))
     return hipErrorInvalidValue;
@@ -1691,41 +1723,48 @@ hipError_t gemm_wgrad_grouped(const WgradProblem* probs, int n, int total_tiles,
   a.group = probs;
   a.group_n = n;
   a.nonfinite = nonfinite;
-  if (wide) {
-    if (overwrite) launch_grouped<PP<256>, EPI_STORE>(a, total_tiles, K, st);
-    else launch_grouped<PP<256>, EPI_ACC>(a, total_tiles, K, st);
-  } else {
-    if (overwrite) launch_grouped<P256x128, EPI_STORE>(a, total_tiles, K, st);
-    else launch_grouped<P256x128, EPI_ACC>(a, total_tiles, K, st);
-  }
+  with_tile(tile, [&](auto cf) {
+    using CF = decltype(cf);
+    if (overwrite) launch_grouped<CF, EPI_STORE>(a, total_tiles, K, st);
+    else launch_grouped<CF, EPI_ACC>(a, total_tiles, K, st);
+  });
   return hipGetLastError();
 }
 
 int gemm_acc_splits(DType dt, int M, int N, int K) {
   // Split-K count for Cf32 += A^T B. Cost model, in microseconds: rounds of
-  // workgroups over the resident slots (CUs x workgroups per CU) times the
-  // k-tiles each runs (about 2.3 TFLOP/s per CU, shared by its workgroups),
-  // plus the fp32 read-modify-write or atomic adds of the epilogue (about
-  // 2 ps per element and split).
-  const bool pipe = dt == DT_BF16 && N % 8 == 0;
-  const int bm = pipe ? P128x128o2::BM : T128x128::BM, bn = pipe ? P128x128o2::BN : T128x128::BN;
-  const int bk = pipe ? 64 : KVN * (dt == DT_BF16 ? 8 : 4);
-  const int occ = pipe ? P128x128o2::OCC : 1;   // workgroups resident per CU
-  const int cus = cu_count() * occ;
-  const double tiles = (double)((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-  const int kt = (K + bk - 1) / bk;
-  const double t_k = 2.0 * bm * bn * bk / (2.3e6 / occ), t_e = 2e-6 * M * N;
-  int best = 1;
-  double best_t = 1e30;
-  for (int sp = 1; sp <= 16 && sp <= kt; sp *= 2) {
-    const double rounds = std::ceil(tiles * sp / cus);
-    const double t = rounds * std::ceil((double)kt / sp) * t_k + sp * t_e;
-    if (t < best_t * 0.97) {
-      best_t = t;
-      best = sp;
+  // workgroups over the resident slots times the k-tiles each runs, plus the
+  // fp32 read-modify-write or atomic adds of the epilogue (about 2 ps per
+  // element and split).
+  auto best_of = [&](auto cost) {
+    int best = 1;
+    double best_t = 1e30;
+    for (int sp = 1; sp <= 16; sp *= 2) {
+      const double t = cost(sp) + sp * 2e-6 * M * N;
+      if (t < best_t * 0.97) {
+        best_t = t;
+        best = sp;
+      }
     }
+    return best;
+  };
+  if (dt == DT_BF16) {
+    // 128 x 128 tiles, two workgroups per CU: about 2.3 TFLOP/s per CU, shared by them
+    constexpr int BM = P128x128o2::BM, BN = P128x128o2::BN, OCC = P128x128o2::OCC;
+    const double tiles = (double)((M + BM - 1) / BM) * ((N + BN - 1) / BN), t_k = 2.0 * BM * BN * 64 / (2.3e6 / OCC);
+    const int kt = (K + 63) / 64;
+    return best_of([&](int sp) {
+      return sp > kt ? 1e30 : std::ceil(tiles * sp / (cu_count() * OCC)) * std::ceil((double)kt / sp) * t_k;
+    });
   }
-  return best;
+  // fp32: k-tiles of 32 on the tile edge launch() takes for that many splits
+  const int kt = (K + 31) / 32;
+  return best_of([&](int sp) {
+    if (sp > kt) return 1e30;
+    const int e = f32_tile(M, N, sp);
+    const double tiles = (double)((M + e - 1) / e) * ((N + e - 1) / e), t_k = e == 128 ? 2.4 : e == 64 ? 0.7 : 0.45;
+    return std::ceil(tiles * sp / (2 * cu_count())) * std::ceil((double)kt / sp) * t_k;
+  });
 }
 
 hipError_t gemm_wgrad(DType dt, const GemmArgs& a, hipStream_t st) {

@@ -88,23 +88,26 @@ struct GemmArgs {
 // bf16 operands: K-major vectors that straddle K read the memory just past K,
 // which must hold zeros (true when K % 8 == 0, or for zero-padded rows).
 
-// Two tile shapes: wide = 256 x 256 (eight 128 x 64 wave tiles), else 256 x 128.
+// Tile shapes of a grouped launch.
+enum WgradTile { WG_256x128 = 0, WG_256x256, WG_128x128, WG_64x64 };
 // overwrite: C_p = A_p^T B_p instead of +=; nonfinite (nullable): set to 1 (a plain
 // store) if any element written is NaN or infinite.
-int wgrad_group_tiles(int M, int N, bool wide);
+int wgrad_group_tiles(int M, int N, WgradTile tile);
 // Workgroup w of a problem runs on XCD w % 8. Each XCD streams the operand
 // panels of the tiles it runs through its own L2, so the launch gives each XCD
 // one block of the tile grid: the split of the grid into 8 equal blocks (xcd_m
 // row bands) that reads the fewest panel bytes per XCD, or 0 if the grid does
 // not split evenly (then the generic XCD-aware order applies). K contracted rows.
-int wgrad_group_xcd_m(int M, int N, int K, bool wide);
-// How many leading problems (of n, shapes M[p] x N[p]) go on wide tiles, the rest
-// in a second launch on 256 x 128 tiles: the split with the fewest rounds of
-// workgroups over the CUs, a wide tile costing 1.8 narrow ones (measured); the
-// whole list on narrow tiles when no split does better.
-int wgrad_group_wide(const int* M, const int* N, int n);
+int wgrad_group_xcd_m(int M, int N, int K, WgradTile tile);
+// How many leading problems (of n, shapes M[p] x N[p]) go on 256 x 256 tiles, and
+// the tile shape `rest` of the others, in a second launch. Groups whose 64 x 64 tiles
+// fill the CUs at most twice take those, groups of at most one round of 128 x 128
+// tiles those; larger ones the split between 256 x 256 and 256 x 128 tiles with the
+// fewest rounds of workgroups over the CUs, a 256 x 256 tile costing 1.8 of the
+// others (measured).
+int wgrad_group_split(const int* M, const int* N, int n, WgradTile* rest);
 hipError_t gemm_wgrad_grouped(const WgradProblem* probs, int n, int total_tiles, int K, const void* zeros,
-                              bool overwrite, bool wide, int* nonfinite, hipStream_t st);
+                              bool overwrite, WgradTile tile, int* nonfinite, hipStream_t st);
 
 // Cf32 += A^T B (GEMM_TN, one problem): large products as whole rounds of 256 x 256
 // tiles (plain read-modify-write) plus the remaining rows, others split over K
@@ -113,13 +116,6 @@ hipError_t gemm_wgrad(DType dt, const GemmArgs& a, hipStream_t st);
 // dtype: element type of A, B, aux and of C/C2 unless out_f32 (then C is float).
 // splits > 1 is only valid with EPI_ATOMIC.
 hipError_t gemm(DType dt, bool out_f32, GemmLayout lay, GemmEpi epi, const GemmArgs& a, int splits, hipStream_t st);
-// Tile edge used by gemm(); callers size split-K against it.
-// Split-K count the fp32-accumulating TN product (weight gradients) should use.
-int gemm_acc_splits(DType dt, int M, int N, int K);
-// Testing hook: force one kernel configuration for bf16 calls (0: register-staged 128x128;
-// direct-to-LDS pipelines 10: 256x128 x 3 stages (the default), 11: 128x128 x 4, 12: 128x256 x 3).
-void gemm_set_tile_override(int cfg);
-
 // ---- causal attention over the fused projection qkv [T, 3d] --------------------------
 // Forward: o [T, d]; lse2 [mu*H*S] = log2-sum-exp2 of the scaled scores in log2 units.
 hipError_t attn_fwd(DType dt, const void* qkv, void* o, float* lse2, int mu, int S, int H, int dh, const DropArgs& drop,

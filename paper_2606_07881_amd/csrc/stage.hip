@@ -332,8 +332,10 @@ struct Layout {
   // gradients to G in one grouped launch at its end
   bool wdefer = false;
   size_t wgroup = 0;           // problem tables of that launch, one per activation slot (or work slot)
-  int wgroup_n = 0, wgroup_tiles = 0;   // problems per table; workgroups of the 256 x 128 launch
+  int wgroup_n = 0, wgroup_tiles = 0;   // problems per table; workgroups of the second launch
+  paci::WgradTile wgroup_rest = paci::WG_256x128;   // its tile shape
   int wgroup_n1 = 0, wgroup_tiles1 = 0; // leading problems on 256 x 256 tiles (their own launch); its workgroups
+  paci::WgradTile wgroup_tile(int p) const { return p < wgroup_n1 ? paci::WG_256x256 : wgroup_rest; }
   // checkpointed stages: each slot holds the stage input only (c_* offsets,
   // c_bytes per slot); one work slot of the full layout takes the activations
   bool recompute = false;
@@ -493,12 +495,10 @@ Layout make_layout(const paci_shapes& s, int K, int delay, const ParamTable& p) 
         Ms.push_back(shapes[q][0]);
         Ns.push_back(shapes[q][1]);
       }
-    L.wgroup_n1 = paci::wgrad_group_wide(Ms.data(), Ns.data(), L.wgroup_n);
+    L.wgroup_n1 = paci::wgrad_group_split(Ms.data(), Ns.data(), L.wgroup_n, &L.wgroup_rest);
     int tiles1 = 0, tiles = 0;
-    for (int p = 0; p < L.wgroup_n; ++p) {
-      const bool wide = p < L.wgroup_n1;
-      (wide ? tiles1 : tiles) += (paci::wgrad_group_tiles(Ms[p], Ns[p], wide) + 7) / 8 * 8;
-    }
+    for (int p = 0; p < L.wgroup_n; ++p)
+      (p < L.wgroup_n1 ? tiles1 : tiles) += (paci::wgrad_group_tiles(Ms[p], Ns[p], L.wgroup_tile(p)) + 7) / 8 * 8;
     L.wgroup_tiles1 = tiles1;
     L.wgroup_tiles = tiles;
   }
@@ -935,15 +935,15 @@ int wgrad_grouped(paci_stage* h, int t, bool overwrite, int* flag) {
   const auto* tab = reinterpret_cast<const paci::WgradProblem*>(h->arena + L.wgroup) + (size_t)t * L.wgroup_n;
   const int n1 = L.wgroup_n1;
   return run(h, F_GEMM_WGRAD, work, [&] {
-    // the leading problems on 256 x 256 tiles, the rest on 256 x 128 (each launch
+    // the leading problems on 256 x 256 tiles, the rest on wgroup_rest (each launch
     // fills whole rounds of the CUs where the shapes allow)
     hipError_t e = hipSuccess;
     if (n1 > 0)
-      e = paci::gemm_wgrad_grouped(tab, n1, L.wgroup_tiles1, (int)L.T, h->arena + L.zeros, overwrite, true, flag,
+      e = paci::gemm_wgrad_grouped(tab, n1, L.wgroup_tiles1, (int)L.T, h->arena + L.zeros, overwrite, paci::WG_256x256, flag,
                                    h->st);
     if (e == hipSuccess && n1 < L.wgroup_n)
       e = paci::gemm_wgrad_grouped(tab + n1, L.wgroup_n - n1, L.wgroup_tiles, (int)L.T, h->arena + L.zeros,
-                                   overwrite, false, flag, h->st);
+                                   overwrite, L.wgroup_rest, flag, h->st);
     return e;
   });
 }
@@ -966,7 +966,7 @@ std::vector<paci::WgradProblem> wgrad_tables(const paci_stage* h) {
   std::vector<paci::WgradProblem> v;
   for (int t = 0; t < tables; ++t) {
     const char* A = L.recompute ? h->arena + L.work : h->arena + L.stash + (size_t)t * L.slot_bytes;
-    int tile0 = 0, p = 0;   // tile0 restarts at the first problem of the 256 x 128 launch
+    int tile0 = 0, p = 0;   // tile0 restarts at the first problem of the second launch
     for (int l = h->s.n_layers - 1; l >= 0; --l) {   // the order the backward produced them
       const BlockRefs& b = h->p.blocks[l];
       const BlockSlot& o = L.blk[l];
@@ -974,7 +974,7 @@ std::vector<paci::WgradProblem> wgrad_tables(const paci_stage* h) {
       const struct { size_t dy, x; int M, N; int64_t g; } q[4] = {
           {w.dy, o.a, d, f, b.w_2}, {w.du, o.n2, f, d, b.w_1}, {w.dx1, o.o, d, d, b.w_o}, {w.dqkv, o.n1, 3 * d, d, b.w_qkv}};
       for (const auto& e : q) {
-        const bool wide = p < L.wgroup_n1;
+        const paci::WgradTile tile = L.wgroup_tile(p);
         if (p++ == L.wgroup_n1) tile0 = 0;
         paci::WgradProblem pr;
         pr.A = h->arena + e.dy;
@@ -983,9 +983,9 @@ std::vector<paci::WgradProblem> wgrad_tables(const paci_stage* h) {
         pr.M = e.M;
         pr.N = e.N;
         pr.tile0 = tile0;
-        pr.xcd_m = paci::wgrad_group_xcd_m(e.M, e.N, (int)L.T, wide);
+        pr.xcd_m = paci::wgrad_group_xcd_m(e.M, e.N, (int)L.T, tile);
         v.push_back(pr);
-        tile0 += (paci::wgrad_group_tiles(e.M, e.N, wide) + 7) / 8 * 8;
+        tile0 += (paci::wgrad_group_tiles(e.M, e.N, tile) + 7) / 8 * 8;
       }
     }
   }

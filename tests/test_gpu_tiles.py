@@ -56,3 +56,17 @@ def test_lm_head(binding, V, d, seq, mu, fused):  # noqa: F811
 @pytest.mark.parametrize("T", [64, 128, 320, 384])
 def test_pingpong_window(binding, T):  # noqa: F811
     _check(binding, small_cfg("win_bf16", d_model=288, n_heads=9, head_dim=32, d_ff=416, seq=T // 2, micro_batch=2))
+
+
+# bf16 products on the tiles of small grids, ragged on every side: 64 x 64 up to
+# one round of the CUs, then 128 x 64 (each epilogue: N = d, 3 d and f), then 128 x 128
+@pytest.mark.parametrize("d,f,seq,mu", [(32, 64, 1, 1), (96, 160, 65, 1), (448, 1792, 33, 3), (320, 992, 100, 11),
+                                        (960, 64, 100, 11), (320, 992, 200, 11), (960, 96, 200, 11)])
+def test_small_grids_bf16(binding, d, f, seq, mu):  # noqa: F811
+    _check(binding, small_cfg("dh32_bf16", d_model=d, n_heads=d // 32, d_ff=f, seq=seq, micro_batch=mu))
+
+
+# fp32 products on 32 x 32, 64 x 64 and 128 x 128 tiles, and split weight gradients
+@pytest.mark.parametrize("d,f,seq,mu", [(32, 64, 1, 1), (96, 160, 65, 1), (64, 2080, 125, 8), (32, 4128, 250, 8)])
+def test_small_grids_fp32(binding, d, f, seq, mu):  # noqa: F811
+    _check(binding, small_cfg("ragged_fp32", n_layers=1, d_model=d, n_heads=d // 32, d_ff=f, seq=seq, micro_batch=mu))
