@@ -322,10 +322,14 @@ __global__ void __launch_bounds__(FwdRing<DH>::NTF, 2) attn_fwd_ring_kernel(cons
       m_run[qs] = m_new;
       if constexpr (DROP) {   // dropout: the product uses P * keep * scale, the normalizer all of P
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt) {
-          const uint32_t bits = drop_row4(drop, bh, qrow, k0 + kt * 16 + 4 * g);
+        for (int kt = 0; kt < 4; kt += 2) {
+          uint32_t bits[2];
+          drop_row4_pair(drop, bh, qrow, k0 + kt * 16 + 4 * g, k0 + kt * 16 + 16 + 4 * g, bits[0], bits[1]);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) sc[qs][kt][r] = ((bits >> r) & 1) ? sc[qs][kt][r] * drop.scale : 0.f;
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              sc[qs][kt + u][r] = ((bits[u] >> r) & 1) ? sc[qs][kt + u][r] * drop.scale : 0.f;
         }
       }
 #pragma unroll
@@ -811,13 +815,7 @@ __device__ __forceinline__ void dkdv_ring_body(u32x4* ring, int kb, const bf16* 
       // P = 2^(s * scale * log2 e - lse2), dS = P (dP - D); masked entries get P = 0.
       // Dropout M = keep * scale: dV takes P M, and dP = (dO V^T) M.
       uint32_t dbits[2][SUB];
-      if constexpr (DROP) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-          for (int ks = 0; ks < SUB; ++ks)
-            dbits[u][ks] = drop_col4(drop, bh, q0 + (2 * s + u) * 16 + 4 * g, kw0 + 16 * ks + (l & 15));
-      }
+      if constexpr (DROP) drop_col4_quad<SUB>(drop, bh, q0 + 32 * s, kw0, dbits);
       auto softmax = [&](auto masked) {
 #pragma unroll
         for (int u = 0; u < 2; ++u)
@@ -989,10 +987,11 @@ __device__ __forceinline__ void dq_ring_body(u32x4* ring, int yb, const bf16* qk
 #pragma unroll
         for (int qs = 0; qs < SUB; ++qs) {
           const int q = qw0 + 16 * qs + (l & 15);
+          uint32_t dbits[2] = {0xfu, 0xfu};   // dropout M = keep * scale on dP = dO V^T
+          if constexpr (DROP) drop_row4_pair(drop, bh, q, k0 + 32 * s + 4 * g, k0 + 32 * s + 16 + 4 * g, dbits[0], dbits[1]);
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            // dropout M = keep * scale on dP = dO V^T
-            const uint32_t bits = DROP ? drop_row4(drop, bh, q, k0 + (2 * s + u) * 16 + 4 * g) : 0xfu;
+            const uint32_t bits = dbits[u];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
               float x = fmaf(sc[qs][u][r], scale_log2, -lq[qs]);

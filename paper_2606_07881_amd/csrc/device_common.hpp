@@ -25,6 +25,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace paci {
@@ -283,6 +285,10 @@ template <int CTRL>
 __device__ __forceinline__ float dpp_f(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
 }
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+}
 __device__ __forceinline__ float row_sum16(float v) {
   v += dpp_f<0xB1>(v);    // quad_perm [1, 0, 3, 2]
   v += dpp_f<0x4E>(v);    // quad_perm [2, 3, 0, 1]
@@ -369,8 +375,8 @@ __device__ __forceinline__ u32x4 philox10(uint32_t c0, uint32_t c1, uint32_t c2,
     }
     const uint32_t hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
     const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
-    c0 = hi1 ^ c1 ^ k0;
-    c2 = hi0 ^ c3 ^ k1;
+    c0 = __builtin_amdgcn_bitop3_b32(hi1, c1, k0, 0x96);   // three-operand exclusive or
+    c2 = __builtin_amdgcn_bitop3_b32(hi0, c3, k1, 0x96);
     c1 = lo1;
     c3 = lo0;
   }
@@ -403,6 +409,64 @@ __device__ __forceinline__ uint32_t drop_col4(const DropArgs& a, uint32_t bh, in
     bits |= keep16(kb ? w[3] : w[2], half, a.thr) << (2 * j + 1);
   }
   return bits;
+}
+
+// The same bits with draws shared between lanes. A draw holds 2 queries x 4 keys
+// and costs 40 32-bit products at a quarter of the vector rate, which is what
+// bounds the attention kernels under dropout. 8192 tokens, 16 heads of 64, 1024
+// keys: backward 101 us without dropout, 214 with every lane drawing for
+// itself, 155 with shared draws (163 before the three-operand exclusive or);
+// forward 45, 91 and 76 (79).
+// Keys k4a .. and k4b .. of query q, where lane parity is query parity and the
+// neighbouring lane (l ^ 1) holds query q ^ 1 and the same keys: the even lane
+// draws k4a, the odd one k4b, and each passes on the half of the other's query.
+__device__ __forceinline__ void drop_row4_pair(const DropArgs& a, uint32_t bh, int q, int k4a, int k4b, uint32_t& bits_a,
+                                               uint32_t& bits_b) {
+  const bool odd = (q & 1) != 0;
+  const u32x4 w = philox10((uint32_t)(odd ? k4b : k4a) >> 2, (uint32_t)q >> 1, bh, a.word, a.seed, a.mb);
+  const uint32_t own0 = odd ? w[2] : w[0], own1 = odd ? w[3] : w[1];
+  const uint32_t oth0 = dpp_u<0xB1>(odd ? w[0] : w[2]), oth1 = dpp_u<0xB1>(odd ? w[1] : w[3]);   // quad_perm [1, 0, 3, 2]
+  auto bits = [&](uint32_t x, uint32_t y) {
+    return keep16(x, 0, a.thr) | (keep16(x, 1, a.thr) << 1) | (keep16(y, 0, a.thr) << 2) | (keep16(y, 1, a.thr) << 3);
+  };
+  bits_a = bits(odd ? oth0 : own0, odd ? oth1 : own1);
+  bits_b = bits(odd ? own0 : oth0, odd ? own1 : oth1);
+}
+// Queries q16 + 16 u + 4 g .. + 3 (u = 0, 1; g = l / 16) of keys k0 + 16 ks + l % 16
+// (ks < SUB; k0 a multiple of 4): bits[u][ks]. The four lanes of a quad hold the
+// four keys of one draw: the 4 SUB draws of a quad are computed SUB to a lane
+// and broadcast.
+template <int SUB>
+__device__ __forceinline__ void drop_col4_quad(const DropArgs& a, uint32_t bh, int q16, int k0, uint32_t (&bits)[2][SUB]) {
+  const int l = lane_id(), i = l & 3, g = l >> 4;
+  u32x4 w[SUB];
+#pragma unroll
+  for (int t = 0; t < SUB; ++t) {   // draw 4 t + i: query pair j = i & 1 of (u, ks)
+    const int v = 2 * t + (i >> 1), ks = v % SUB, u = v / SUB;
+    const int k = k0 + 16 * ks + (l & 12), q = q16 + 16 * u + 4 * g;
+    w[t] = philox10((uint32_t)k >> 2, ((uint32_t)q >> 1) + (i & 1), bh, a.word, a.seed, a.mb);
+  }
+  const bool kb = (i >> 1) != 0;
+  const int sh = 16 * (i & 1);
+  auto keep = [&](uint32_t x) { return ((x >> sh) & 0xffffu) >= a.thr ? 1u : 0u; };
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int ks = 0; ks < SUB; ++ks) bits[u][ks] = 0;
+#pragma unroll
+  for (int t = 0; t < SUB; ++t) {
+    auto take = [&](auto o) {
+      constexpr int O = decltype(o)::value, J = O & 1;
+      const int v = 2 * t + (O >> 1), ks = v % SUB, u = v / SUB;
+      const uint32_t w0 = dpp_u<O * 0x55>(w[t][0]), w1 = dpp_u<O * 0x55>(w[t][1]);
+      const uint32_t w2 = dpp_u<O * 0x55>(w[t][2]), w3 = dpp_u<O * 0x55>(w[t][3]);
+      bits[u][ks] |= (keep(kb ? w1 : w0) << (2 * J)) | (keep(kb ? w3 : w2) << (2 * J + 1));
+    };
+    take(std::integral_constant<int, 0>{});
+    take(std::integral_constant<int, 1>{});
+    take(std::integral_constant<int, 2>{});
+    take(std::integral_constant<int, 3>{});
+  }
 }
 // bit i: element e8 + i, i < 8, e8 % 8 == 0 (one draw)
 __device__ __forceinline__ uint32_t drop_elem8(const DropArgs& a, uint64_t e8) {

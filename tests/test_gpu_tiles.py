@@ -70,3 +70,12 @@ def test_small_grids_bf16(binding, d, f, seq, mu):  # noqa: F811
 @pytest.mark.parametrize("d,f,seq,mu", [(32, 64, 1, 1), (96, 160, 65, 1), (64, 2080, 125, 8), (32, 4128, 250, 8)])
 def test_small_grids_fp32(binding, d, f, seq, mu):  # noqa: F811
     _check(binding, small_cfg("ragged_fp32", n_layers=1, d_model=d, n_heads=d // 32, d_ff=f, seq=seq, micro_batch=mu))
+
+
+# dropout draws shared between lanes (two queries x four keys per draw) at each
+# head dim, with key and query counts that end inside a draw, a 16-row tile and a block
+@pytest.mark.parametrize("dh", [32, 64, 128])
+@pytest.mark.parametrize("seq", [1, 2, 5, 63, 66, 131])
+def test_dropout_draws(binding, dh, seq):  # noqa: F811
+    _check(binding, small_cfg("drop_ragged_bf16", n_layers=1, d_model=2 * dh, n_heads=2, head_dim=dh, d_ff=64, seq=seq,
+                              micro_batch=2))
