@@ -1528,19 +1528,23 @@ hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
           if (tiles(128, 128) <= cus) return launch_pipe<TO, AK, BK, EPI, P128x128w8>(a, splits, st);
         }
       }
-      // The FFN up-projection and the input gradient through gelu'(u):
-      // 256 x 256 ping-pong tiles when they fill whole rounds of the CUs
-      // (at 8192 x 4096 x 1024, in the stage: 106 us on 256 x 128 tiles,
-      // 90.6 on 256 x 256 ring tiles, 88.9 ping-pong; the input gradient
-      // 110, 88.9 and 82.2). Otherwise weight gradients (both operands
-      // MN-major) and the input gradient through gelu'(u): 128 x 128
-      // tiles, two workgroups per CU, so one's epilogue overlaps the
-      // other's loop (3-6% faster for the latter, slower for the other
-      // forward and input-gradient products); the rest: 256 x 128 tiles,
-      // which re-read the weights half as often.
-      if constexpr (AK && BK && (EPI == EPI_BIAS_GELU || EPI == EPI_GELU_GRAD)) {
-        const int t256 = ((a.M + 255) / 256) * ((a.N + 255) / 256);
-        if (splits == 1 && t256 % cu_count() == 0) return launch_pp<TO, AK, BK, EPI, 256>(a, splits, st);
+      // 256 x 256 ping-pong tiles where they take fewer rounds of the CUs than
+      // 256 x 128 ring tiles, a round of them costing 1.8 of the others (whole
+      // rounds at 8192 x 4096 x 1024, in the stage: FFN1 forward 106 -> 88.9 us,
+      // FFN2 input gradient 110 -> 82.2; at 8192 x 2048, mean of K 2048 and
+      // 8192: residual 163 -> 131, plain 157 -> 131; qkv 8192 x 6144 x 2048:
+      // 209 -> 170).
+      // Otherwise weight gradients (both operands MN-major) and the input
+      // gradient through gelu'(u): 128 x 128 tiles, two workgroups per CU, so
+      // one's epilogue overlaps the other's loop (3-6% faster for the latter,
+      // slower for the other forward and input-gradient products: qkv 67 -> 69
+      // us); the rest: 256 x 128 tiles, which re-read the weights half as often.
+      if constexpr (AK && BK && sizeof(TO) == 2) {
+        auto rounds = [&](int bn) {
+          const int64_t t = (int64_t)((a.M + 255) / 256) * ((a.N + bn - 1) / bn);
+          return (double)((t + cu_count() - 1) / cu_count());
+        };
+        if (splits == 1 && 1.8 * rounds(256) < rounds(128)) return launch_pp<TO, AK, BK, EPI, 256>(a, splits, st);
       }
       // An MN-major weight operand (the LM head's input gradient, K = V):
       // 256 x 128 ping-pong tiles, whose partial last k-tile does not slow

@@ -27,6 +27,13 @@ def test_pingpong_kmajor(binding, d):  # noqa: F811
     _check(binding, small_cfg("tall_bf16", d_model=d, n_heads=d // 32))
 
 
+# the same tiles in every forward and input-gradient product of a block (T
+# 16600: 65 row tiles, two rounds of 256 x 128 tiles against one of 256 x 256)
+@pytest.mark.parametrize("d", [480, 512])
+def test_pingpong_all_products(binding, d):  # noqa: F811
+    _check(binding, small_cfg("dh32_bf16", d_model=d, n_heads=d // 32, d_ff=64, seq=83, micro_batch=200))
+
+
 # the same tiles with both operands MN-major (grouped weight gradients): 1 to 4
 # k-tiles over T, T a multiple of 8 or odd
 @pytest.mark.parametrize("seq,mu", [(20, 2), (64, 1), (36, 2), (25, 3), (64, 2), (67, 3)])
