@@ -16,6 +16,7 @@
 // contiguous range of tiles, walked in groups of 8 tile-rows to keep A and B
 // panels in that XCD's L2.
 #include "device_common.hpp"
+#include <algorithm>
 #include <cmath>
 
 #include "kernels.hpp"
@@ -968,9 +969,9 @@ __global__ void __launch_bounds__(CF::NT, CF::OCC) gemm_pipe_kernel(GemmArgs a, 
 // 1.6-1.9 GHz: 1270 -> 1500 TFLOP/s on an 8192^3 product, where zeros run at
 // 2.36 GHz and 1830. 256 x 128 tiles reach 1290 cycles against 1024 in the same
 // product, but in the stage their loads come from beyond L2 and the deeper
-// prefetch of the ring kernel wins (qkv 67 against 68-74 us), so only the
-// window products, whose operands are long, take them (207 -> 196 us at
-// 3072 x 768 x 32768).
+// prefetch of the ring kernel wins (qkv 67 against 68-74 us), so only the LM
+// head's input gradient and narrow window products, whose contractions are
+// long, take them.
 //
 // Ordering. A wavefront waits for its LDS reads at the start of the matrix slot
 // that follows them, so a sub-tile read by group 1 in slot s (group 0 is one
@@ -1487,6 +1488,33 @@ bool pipe_eligible(const GemmArgs& a) {
          a.lda < (1 << 22) && a.ldb < (1 << 22) && (AK || covers(a.lda, a.M)) && (BK || covers(a.ldb, a.N));
 }
 
+// Tiles and split-K count of a window weight gradient: long contractions over
+// few output tiles, so K is split until one round of workgroups (the CUs) is
+// full, each split at least 512 rows, and of the two tile widths the one with
+// the least work per CU is taken, a 256 x 256 tile costing 1.8 of 256 x 128.
+// Atomic adds grow with the splits, at most 32. At 768-wide blocks over 32768
+// rows: 3072 x 768 in 207 us with the three-stage ring on 256 x 128 tiles (two
+// rounds), 196 ping-pong, 172 on 252 of 256 x 256; 2304 x 768 170, 160, 138; 768
+// x 768 114, 112, 93. About 60 us of each are the atomic adds, which cross the
+// XCDs in memory.
+struct WindowPlan { int bn, splits; };
+WindowPlan window_plan(int M, int N, int64_t K) {
+  WindowPlan best{128, 1};
+  double best_t = 1e30;
+  const int cus = cu_count();
+  for (int bn : {256, 128}) {
+    const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + bn - 1) / bn), kt = (K + 63) / 64;
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(32, K / 512));
+    const int sp = (int)std::max<int64_t>(1, std::min(most, cus / tiles));
+    const double t = (double)((tiles * sp + cus - 1) / cus) * (double)((kt + sp - 1) / sp) * (bn == 256 ? 1.8 : 1.0);
+    if (t < best_t) {
+      best_t = t;
+      best = {bn, sp};
+    }
+  }
+  return best;
+}
+
 // fp32 products: the largest tile edge that still gives two workgroups per CU,
 // else the smallest. A 256 x 128 product over 512 runs two 128 x 128 tiles on
 // the whole chip, or 32 of 32 x 32: 33 -> 8.4 us a launch over its calls with
@@ -1501,12 +1529,11 @@ int f32_tile(int M, int N, int splits) {
 template <typename T, typename TO, bool AK, bool BK, int EPI>
 hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
   if (a.seg_rows > 0) {
-    // segmented B (the window weight gradients): 256 x 128 ping-pong tiles
-    // (768-wide stage, 32768 rows: 207, 170 and 114 us per product with the
-    // three-stage ring, 196, 160 and 112 now)
+    // segmented B (the window weight gradients): ping-pong tiles, see gemm_window_splits
     if constexpr (sizeof(T) == 2 && !AK && !BK) {
       if (pipe_eligible<AK, BK>(a) && a.seg_rows % 64 == 0 && a.seg_count >= 1 && a.seg_first >= 0)
-        return launch_pp<TO, AK, BK, EPI, 128>(a, splits, st);
+        return window_plan(a.M, a.N, a.K).bn == 256 ? launch_pp<TO, AK, BK, EPI, 256>(a, splits, st)
+                                                    : launch_pp<TO, AK, BK, EPI, 128>(a, splits, st);
     }
     return hipErrorInvalidValue;
   }
@@ -1770,6 +1797,8 @@ int gemm_acc_splits(DType dt, int M, int N, int K) {
     return std::ceil(tiles * sp / (2 * cu_count())) * std::ceil((double)kt / sp) * t_k;
   });
 }
+
+int gemm_window_splits(int M, int N, int64_t K) { return window_plan(M, N, K).splits; }
 
 hipError_t gemm_wgrad(DType dt, const GemmArgs& a, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0 || a.K <= 0 || a.colsum != nullptr || a.seg_rows > 0) return hipErrorInvalidValue;

@@ -116,6 +116,9 @@ hipError_t gemm_wgrad(DType dt, const GemmArgs& a, hipStream_t st);
 // dtype: element type of A, B, aux and of C/C2 unless out_f32 (then C is float).
 // splits > 1 is only valid with EPI_ATOMIC.
 hipError_t gemm(DType dt, bool out_f32, GemmLayout lay, GemmEpi epi, const GemmArgs& a, int splits, hipStream_t st);
+// Split-K count of a window weight gradient (GEMM_TN, segmented B) over K rows.
+int gemm_window_splits(int M, int N, int64_t K);
+
 // ---- causal attention over the fused projection qkv [T, 3d] --------------------------
 // Forward: o [T, d]; lse2 [mu*H*S] = log2-sum-exp2 of the scaled scores in log2 units.
 hipError_t attn_fwd(DType dt, const void* qkv, void* o, float* lse2, int mu, int S, int H, int dh, const DropArgs& drop,

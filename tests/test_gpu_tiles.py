@@ -59,10 +59,11 @@ def test_lm_head(binding, V, d, seq, mu, fused):  # noqa: F811
                               micro_batch=mu, fused_head=fused))
 
 
-# 256 x 128 ping-pong tiles over segments (window products): 1 to 6 k-tiles, one micro-batch
-@pytest.mark.parametrize("T", [64, 128, 320, 384])
-def test_pingpong_window(binding, T):  # noqa: F811
-    _check(binding, small_cfg("win_bf16", d_model=288, n_heads=9, head_dim=32, d_ff=416, seq=T // 2, micro_batch=2))
+# ping-pong tiles over segments (window products): 1 to 6 k-tiles, one micro-batch,
+# 256 x 256 tiles, 256 x 128 (d 96 and 288), split over K (T 1088)
+@pytest.mark.parametrize("d,T", [(288, 64), (288, 128), (288, 320), (96, 384), (512, 384), (512, 1088)])
+def test_pingpong_window(binding, d, T):  # noqa: F811
+    _check(binding, small_cfg("win_bf16", d_model=d, n_heads=d // 32, head_dim=32, d_ff=416, seq=T // 2, micro_batch=2))
 
 
 # bf16 products on the tiles of small grids, ragged on every side: 64 x 64 up to
