@@ -198,9 +198,15 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 // Forward, bf16: a workgroup takes 64 * QS * 4 queries, each wavefront 16 * QS
 // of them (QS sub-tiles of 16, the query in the lane as in the kernel above),
 // so every K and V fragment read from LDS feeds QS MFMAs. Key blocks are 64.
-template <int DH> struct FwdRing {
+// SMALL: 64 queries, 16 to each of 4 wavefronts, for grids that would leave CUs
+// idle: a workgroup walks its key blocks one after the other, so with less work
+// per block it ends sooner. One sequence of 1024 keys, 12 heads of 64: 48
+// workgroups, 27.1 us; 192 small ones, 16.6 (backward 28.7 -> 24.6); 2 x 200
+// keys, 3 heads: 10.8 -> 6.1 (13.0 -> 10.9).
+template <int DH, bool SMALL = false> struct FwdRing {
   static constexpr int CPR = DH / 8, KS = DH / 32;
-  static constexpr int QS = DH == 32 ? 4 : (DH == 64 ? 2 : 1), WAVES = DH == 32 ? 4 : 8, NTF = 64 * WAVES;
+  static constexpr int QS = SMALL ? 1 : DH == 32 ? 4 : (DH == 64 ? 2 : 1), WAVES = SMALL || DH == 32 ? 4 : 8,
+                       NTF = 64 * WAVES;
   static constexpr int WQ = 16 * QS, BQ = WAVES * WQ;
   // blocks kb (V) and kb + 1 (K) are read in the same iteration, kb + 2 loads
   static constexpr int NS = 4;
@@ -214,10 +220,10 @@ template <int DH> struct FwdRing {
 // unit is not idle during the exponentials. A wavefront's queries start at a multiple of 16 * QS, which
 // divides 64, so every key block before its last one ends before its first
 // query and inside the sequence: only the last block is masked.
-template <int DH, bool DROP>
-__global__ void __launch_bounds__(FwdRing<DH>::NTF, 2) attn_fwd_ring_kernel(const bf16* qkv, bf16* out, float* lse2, int S, int H,
+template <int DH, bool DROP, bool SMALL>
+__global__ void __launch_bounds__((FwdRing<DH, SMALL>::NTF), 2) attn_fwd_ring_kernel(const bf16* qkv, bf16* out, float* lse2, int S, int H,
                                                                int d, float scale_log2, DropArgs drop) {
-  using C = FwdRing<DH>;
+  using C = FwdRing<DH, SMALL>;
   constexpr int QS = C::QS, KS = C::KS, NS = C::NS, CPR = C::CPR;
   __shared__ u32x4 ring[NS * 2 * C::BLK];
   const int nqb = (S + C::BQ - 1) / C::BQ;
@@ -648,10 +654,12 @@ __global__ void __launch_bounds__(NT) attn_bwd_dq_kernel(const T* qkv, const T* 
 // VALU work overlaps the other's MFMAs (one workgroup of 8 wavefronts per CU
 // keeps them in step: 9% slower for dK/dV, 4% for dQ). 128: 8 of 16 rows;
 // 32: 4 of 64 rows.
-template <int DH> struct BwdRing {
+// SMALL: 4 wavefronts of 16 rows, for grids that would leave CUs idle.
+template <int DH, bool SMALL = false> struct BwdRing {
   static constexpr int CPR = DH / 8, KST = DH / 32;
-  static constexpr int SUB = DH == 32 ? 4 : (DH == 64 ? 2 : 1), WAVES = DH == 128 ? 8 : 4, NTB = 64 * WAVES;
-  static constexpr int OCC = DH == 32 ? 1 : 2;   // wavefronts per SIMD the register budget must allow
+  static constexpr int SUB = SMALL ? 1 : DH == 32 ? 4 : (DH == 64 ? 2 : 1), WAVES = DH == 128 && !SMALL ? 8 : 4,
+                       NTB = 64 * WAVES;
+  static constexpr int OCC = DH == 32 && !SMALL ? 1 : 2;   // wavefronts per SIMD the register budget must allow
   static constexpr int WR = 16 * SUB, BR = WAVES * WR;
   static constexpr int NS = 4;
   static constexpr int BLK = 64 * CPR;
@@ -731,11 +739,11 @@ __device__ __forceinline__ void colsum_tiles(float (&v)[NCOL / 16][4], float* re
 }
 
 // dK/dV of key block kb (ring: NS * STAGE slots of LDS)
-template <int DH, bool DROP>
+template <int DH, bool DROP, bool SMALL>
 __device__ __forceinline__ void dkdv_ring_body(u32x4* ring, int kb, const bf16* qkv, const bf16* dO,
                                                const float* pairs, bf16* dqkv, int S, int S_pad, int H, int d,
                                                float scale_log2, float scale, float* gbias, const DropArgs& drop) {
-  using C = BwdRing<DH>;
+  using C = BwdRing<DH, SMALL>;
   constexpr int SUB = C::SUB, KST = C::KST, NS = C::NS, CPR = C::CPR;
   static_assert(NS * C::STAGE * 4 >= C::WAVES * 2 * DH, "LDS for the column sums");
   const int bh = blockIdx.x, b = bh / H, h = bh % H;
@@ -899,11 +907,11 @@ __device__ __forceinline__ void dkdv_ring_body(u32x4* ring, int kb, const bf16* 
 }
 
 // dQ of query block nqb - 1 - yb (ring: NS * 2 * BLK slots of LDS)
-template <int DH, bool DROP>
+template <int DH, bool DROP, bool SMALL>
 __device__ __forceinline__ void dq_ring_body(u32x4* ring, int yb, const bf16* qkv, const bf16* dO,
                                              const float* pairs, bf16* dqkv, int S, int S_pad, int H, int d,
                                              float scale_log2, float scale, float* gbias, const DropArgs& drop) {
-  using C = BwdRing<DH>;
+  using C = BwdRing<DH, SMALL>;
   constexpr int SUB = C::SUB, KST = C::KST, NS = C::NS, CPR = C::CPR;
   static_assert(NS * 2 * C::BLK * 4 >= C::WAVES * DH, "LDS for the column sums");
   const int nqb = (S + C::BR - 1) / C::BR;
@@ -1051,20 +1059,26 @@ __device__ __forceinline__ void dq_ring_body(u32x4* ring, int yb, const bf16* qk
 // block y, smallest keys first; the rest: dQ, largest queries first), so that
 // the tail of the dK/dV blocks overlaps the first dQ blocks and the two share
 // CUs (7% faster than two launches at head dim 64).
-template <int DH, bool DROP>
-__global__ void __launch_bounds__(BwdRing<DH>::NTB, BwdRing<DH>::OCC) attn_bwd_ring_kernel(const bf16* qkv, const bf16* dO, const float* pairs,
+template <int DH, bool DROP, bool SMALL>
+__global__ void __launch_bounds__((BwdRing<DH, SMALL>::NTB), (BwdRing<DH, SMALL>::OCC)) attn_bwd_ring_kernel(const bf16* qkv, const bf16* dO, const float* pairs,
                                                                bf16* dqkv, int S, int S_pad, int H, int d,
                                                                float scale_log2, float scale, float* gbias,
                                                                DropArgs drop, int ny) {
-  using C = BwdRing<DH>;
+  using C = BwdRing<DH, SMALL>;
   constexpr int SLOTS = C::STAGE > 2 * C::BLK ? C::NS * C::STAGE : C::NS * 2 * C::BLK;
   __shared__ u32x4 ring[SLOTS];
   if ((int)blockIdx.y < ny)
-    dkdv_ring_body<DH, DROP>(ring, blockIdx.y, qkv, dO, pairs, dqkv, S, S_pad, H, d, scale_log2, scale, gbias, drop);
+    dkdv_ring_body<DH, DROP, SMALL>(ring, blockIdx.y, qkv, dO, pairs, dqkv, S, S_pad, H, d, scale_log2, scale, gbias, drop);
   else
-    dq_ring_body<DH, DROP>(ring, blockIdx.y - ny, qkv, dO, pairs, dqkv, S, S_pad, H, d, scale_log2, scale, gbias,
+    dq_ring_body<DH, DROP, SMALL>(ring, blockIdx.y - ny, qkv, dO, pairs, dqkv, S, S_pad, H, d, scale_log2, scale, gbias,
                            drop);
 }
+
+// Whether workgroups of 64 rows (SMALL) fit the CUs about twice, so that the
+// larger ones (2 to 4 times the rows) would not fill them: heads * ceil(S / 64)
+// workgroups. Above that the larger ones share each K and V (Q and dO) fragment
+// between more rows.
+bool small_grid(int64_t heads, int S) { return heads * ((S + 63) / 64) <= 2 * cu_count(); }
 
 template <typename T, int DH>
 hipError_t fwd_launch(const void* qkv, void* o, float* lse2, int mu, int S, int H, const DropArgs& drop,
@@ -1072,15 +1086,16 @@ hipError_t fwd_launch(const void* qkv, void* o, float* lse2, int mu, int S, int 
   const int d = H * DH;
   const float scale_log2 = LOG2E / sqrtf((float)DH);
   if constexpr (sizeof(T) == 2) {
-    using C = FwdRing<DH>;
-    dim3 grid(mu * H, (S + C::BQ - 1) / C::BQ);   // x fastest: every head's heaviest query block first
-    if (drop.thr)
-      hipLaunchKernelGGL((attn_fwd_ring_kernel<DH, true>), grid, dim3(C::NTF), 0, st,
-                         reinterpret_cast<const bf16*>(qkv), reinterpret_cast<bf16*>(o), lse2, S, H, d, scale_log2, drop);
-    else
-      hipLaunchKernelGGL((attn_fwd_ring_kernel<DH, false>), grid, dim3(C::NTF), 0, st,
-                         reinterpret_cast<const bf16*>(qkv), reinterpret_cast<bf16*>(o), lse2, S, H, d, scale_log2, drop);
-    return hipGetLastError();
+    auto go = [&](auto small) {
+      constexpr bool SM = decltype(small)::value;
+      using C = FwdRing<DH, SM>;
+      dim3 grid(mu * H, (S + C::BQ - 1) / C::BQ);   // x fastest: every head's heaviest query block first
+      auto k = drop.thr ? attn_fwd_ring_kernel<DH, true, SM> : attn_fwd_ring_kernel<DH, false, SM>;
+      hipLaunchKernelGGL(k, grid, dim3(C::NTF), 0, st, reinterpret_cast<const bf16*>(qkv), reinterpret_cast<bf16*>(o),
+                         lse2, S, H, d, scale_log2, drop);
+      return hipGetLastError();
+    };
+    return small_grid(mu * H, S) ? go(std::true_type{}) : go(std::false_type{});
   }
   dim3 grid((S + 63) / 64, mu * H);
   if (drop.thr)
@@ -1099,7 +1114,6 @@ hipError_t bwd_launch(const void* qkv, const void* o, const void* dO, const floa
   const float scale = 1.f / sqrtf((float)DH);
   const float scale_log2 = LOG2E * scale;
   if constexpr (sizeof(T) == 2) {
-    using C = BwdRing<DH>;
     const int S_pad = (S + 63) / 64 * 64;
     const int64_t rows = (int64_t)mu * S * H;
     const int64_t threads = (rows + PAIR_ROWS - 1) / PAIR_ROWS * (DH / 8);
@@ -1112,15 +1126,16 @@ hipError_t bwd_launch(const void* qkv, const void* o, const void* dO, const floa
                        reinterpret_cast<const bf16*>(o), g, lse2, Dbuf, S, S_pad, H, d, rows);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int ny = (S + C::BR - 1) / C::BR;
-    const dim3 grid(mu * H, 2 * ny);   // dK/dV blocks, then dQ blocks
-    if (drop.thr)
-      hipLaunchKernelGGL((attn_bwd_ring_kernel<DH, true>), grid, dim3(C::NTB), 0, st, q, g, Dbuf, dq, S, S_pad, H, d,
-                         scale_log2, scale, gbias, drop, ny);
-    else
-      hipLaunchKernelGGL((attn_bwd_ring_kernel<DH, false>), grid, dim3(C::NTB), 0, st, q, g, Dbuf, dq, S, S_pad, H, d,
-                         scale_log2, scale, gbias, drop, ny);
-    return hipGetLastError();
+    auto go = [&](auto small) {
+      constexpr bool SM = decltype(small)::value;
+      using C = BwdRing<DH, SM>;
+      const int ny = (S + C::BR - 1) / C::BR;
+      const dim3 grid(mu * H, 2 * ny);   // dK/dV blocks, then dQ blocks
+      auto k = drop.thr ? attn_bwd_ring_kernel<DH, true, SM> : attn_bwd_ring_kernel<DH, false, SM>;
+      hipLaunchKernelGGL(k, grid, dim3(C::NTB), 0, st, q, g, Dbuf, dq, S, S_pad, H, d, scale_log2, scale, gbias, drop, ny);
+      return hipGetLastError();
+    };
+    return small_grid(2 * mu * H, S) ? go(std::true_type{}) : go(std::false_type{});
   }
   constexpr int LPR = DH / Vec<T>::V;
   const int64_t rows = (int64_t)mu * S * H;

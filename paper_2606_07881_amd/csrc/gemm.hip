@@ -22,6 +22,20 @@
 #include "kernels.hpp"
 
 namespace paci {
+
+int cu_count() {
+  static int cus = 0;
+  if (cus == 0) {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) ==
+                                                hipSuccess && n > 0)
+      cus = n;
+    else
+      cus = 256;
+  }
+  return cus;
+}
+
 namespace {
 
 constexpr int KVN = 8, GROUP_M = 8;
@@ -1446,18 +1460,6 @@ hipError_t launch_pp(const GemmArgs& a, int splits, hipStream_t st) {
   return hipGetLastError();
 }
 
-int cu_count() {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) ==
-                                                hipSuccess && n > 0)
-      cus = n;
-    else
-      cus = 256;
-  }
-  return cus;
-}
 
 template <typename T, typename TO, bool AK, bool BK, int EPI, class CF>
 hipError_t launch_cf(const GemmArgs& a, int splits, hipStream_t st) {

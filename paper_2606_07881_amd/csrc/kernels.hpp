@@ -8,6 +8,9 @@ namespace paci {
 
 enum DType { DT_F32 = 0, DT_BF16 = 1 };
 
+// Compute units of the current device (256 if it cannot be asked).
+int cu_count();
+
 // Dropout at one site of one micro-batch: key (seed, mb), site word
 // (block << 2) | site (0 embedding, 1 attention probabilities, 2 projection
 // output, 3 FFN output); an element is kept when its 16-bit Philox value is

@@ -87,3 +87,11 @@ def test_small_grids_fp32(binding, d, f, seq, mu):  # noqa: F811
 def test_dropout_draws(binding, dh, seq):  # noqa: F811
     _check(binding, small_cfg("drop_ragged_bf16", n_layers=1, d_model=2 * dh, n_heads=2, head_dim=dh, d_ff=64, seq=seq,
                               micro_batch=2))
+
+
+# attention on the larger workgroups (more than two rounds of 64-row ones: 120
+# heads of 300 rows), whose last blocks are ragged; small grids are everywhere else
+@pytest.mark.parametrize("name", ["ragged_bf16", "drop_ragged_bf16"])
+@pytest.mark.parametrize("dh", [32, 64, 128])
+def test_attention_large_grid(binding, dh, name):  # noqa: F811
+    _check(binding, small_cfg(name, n_layers=1, d_model=4 * dh, n_heads=4, head_dim=dh, d_ff=64, seq=300, micro_batch=30))
