@@ -1569,11 +1569,32 @@ hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
       // slower for the other forward and input-gradient products: qkv 67 -> 69
       // us); the rest: 256 x 128 tiles, which re-read the weights half as often.
       if constexpr (AK && BK && sizeof(TO) == 2) {
-        auto rounds = [&](int bn) {
-          const int64_t t = (int64_t)((a.M + 255) / 256) * ((a.N + bn - 1) / bn);
-          return (double)((t + cu_count() - 1) / cu_count());
-        };
-        if (splits == 1 && 1.8 * rounds(256) < rounds(128)) return launch_pp<TO, AK, BK, EPI, 256>(a, splits, st);
+        const int64_t tm = (a.M + 255) / 256, cus = cu_count();
+        auto rounds = [&](int64_t n, int bn) { return (double)((tm * ((n + bn - 1) / bn) + cus - 1) / cus); };
+        if (splits == 1) {
+          const double wide = 1.8 * rounds(a.N, 256), narrow = rounds(a.N, 128);
+          // Columns of whole 256 x 256 rounds, the others in a launch of their own:
+          // 8192 x 3072 as 2048 + 1024, at K 1024 qkv 67 -> 36.9 + 23.4 us; at K
+          // 768 FFN1 forward 68.6 -> 39.3 + 24.4, FFN2 input gradient 65 -> 36.4 +
+          // 25.0; qkv 8192 x 2304 x 768 (2048 + 256) 54.5 -> 29.9 + 9.5.
+          const int64_t per = cus % tm == 0 ? cus / tm * 256 : 0, n1 = per > 0 ? a.N / per * per : 0;
+          if (n1 > 0 && n1 < a.N && 1.8 * rounds(n1, 256) + rounds(a.N - n1, 128) + 0.1 < std::min(wide, narrow)) {
+            GemmArgs r = a;
+            r.N = (int)n1;
+            const hipError_t e = launch<T, TO, AK, BK, EPI>(r, 1, st);
+            if (e != hipSuccess) return e;
+            auto skip = [&](auto* p) { return p == nullptr ? p : p + n1; };
+            r.N = a.N - (int)n1;
+            r.B = reinterpret_cast<const T*>(a.B) + n1 * a.ldb;
+            r.C = reinterpret_cast<TO*>(a.C) + n1;
+            r.C2 = skip(reinterpret_cast<TO*>(a.C2));
+            r.bias = skip(a.bias);
+            r.aux = skip(reinterpret_cast<const T*>(a.aux));
+            r.colsum = skip(a.colsum);
+            return launch<T, TO, AK, BK, EPI>(r, 1, st);
+          }
+          if (wide < narrow) return launch_pp<TO, AK, BK, EPI, 256>(a, splits, st);
+        }
       }
       // An MN-major weight operand (the LM head's input gradient, K = V):
       // 256 x 128 ping-pong tiles, whose partial last k-tile does not slow

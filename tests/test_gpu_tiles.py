@@ -34,6 +34,12 @@ def test_pingpong_all_products(binding, d):  # noqa: F811
     _check(binding, small_cfg("dh32_bf16", d_model=d, n_heads=d // 32, d_ff=64, seq=83, micro_batch=200))
 
 
+# products split by columns (T 16200: 64 row tiles; N 1440 as 1024 in one round of
+# 256 x 256 tiles and 416 apart): bias, GELU, and gelu' with its column sums
+def test_column_split(binding):  # noqa: F811
+    _check(binding, small_cfg("dh32_bf16", d_model=480, n_heads=15, d_ff=1440, seq=81, micro_batch=200))
+
+
 # the same tiles with both operands MN-major (grouped weight gradients): 1 to 4
 # k-tiles over T, T a multiple of 8 or odd
 @pytest.mark.parametrize("seq,mu", [(20, 2), (64, 1), (36, 2), (25, 3), (64, 2), (67, 3)])
