@@ -27,12 +27,10 @@ COPY_BYTES = 256 * 2 ** 20   # read and written by one copy16 dispatch of stage_
 # Kernel families of the stage library (paci_kernel_family_name) and the
 # kernels (demangled name fragments) one launch of the family runs.
 FAMILIES = {
-    "gemm_fwd": ["gemm_pipe_kernel<bool _Accum, bool, E, true, 1", "gemm_pipe_kernel<bool _Accum, bool, E, true, 2",
-                 "gemm_pipe_kernel<bool _Accum, bool, E, true, 3"],
-    "gemm_dgrad": ["gemm_pipe_kernel<bool _Accum, bool, E, true, 0", "gemm_pipe_kernel<bool _Accum, bool, E, true, 4",
-                   "gemm_pipe_kernel<bool _Accum, bool, E, false, 0", "gemm_pipe_kernel<bool _Accum, bool, E, false, 4"],
-    "gemm_wgrad_acc": ["gemm_pipe_kernel<float, false, false, 5", "gemm_pipe_kernel<float, false, false, 6",
-                       "gemm_pipe_kernel<float, false, false, 0"],
+    "gemm_fwd": [f"gemm_{k}_kernel<bool _Accum, bool, E, true, {e}" for k in ("pipe", "pp") for e in (1, 2, 3)],
+    "gemm_dgrad": [f"gemm_{k}_kernel<bool _Accum, bool, E, {b}, {e}" for k in ("pipe", "pp") for b in ("true", "false")
+                   for e in (0, 4)],
+    "gemm_wgrad_acc": [f"gemm_{k}_kernel<float, false, false, {e}" for k in ("pipe", "pp") for e in (5, 6, 0)],
     "attn_fwd": ["attn_fwd_ring_kernel"],
     "attn_bwd": ["attn_pairs_kernel", "attn_bwd_ring_kernel"],
     "layernorm_fwd": ["ln_fwd_kernel"],
@@ -44,10 +42,12 @@ FAMILIES = {
 # families whose launch runs each of its kernels once; every other family runs
 # one of its kernels (an epilogue or shape variant) per launch
 SEQUENCES = {"attn_bwd", "layernorm_bwd"}
-# families whose launch can run a second kernel of another tile shape (the
-# grouped weight gradients: a 256 x 256 part, then the 256 x 128 rest): a launch
-# is counted once, by its 256 x 128 kernel when the run has one
-SPLIT_LAUNCH = {"gemm_wgrad_acc": "PipeTile<256, 128"}
+# launches that run two kernels of different tile shapes: (family, first, second)
+# name fragments, counted by the second where the run has it (the grouped weight
+# gradients: a 256 x 256 part, then the rest; qkv forward: columns of whole
+# 256 x 256 rounds, then the rest)
+FIRST_OF_TWO = [("gemm_wgrad_acc", "gemm_pp_kernel<float, false, false", "gemm_pipe_kernel<float, false, false"),
+                ("gemm_fwd", "gemm_pp_kernel<bool _Accum, bool, E, true, 1", "gemm_pipe_kernel<bool _Accum, bool, E, true, 1")]
 
 
 def sources_sha256():
@@ -100,7 +100,7 @@ def traffic(fetch_csv, write_csv, copy_bytes=COPY_BYTES):
     w_scale = copy_bytes / (1024.0 * sum(w[copy[0]]) / len(w[copy[0]]))
     fams = collections.defaultdict(float)
     launches = collections.defaultdict(int)
-    split = {fam for fam, tag in SPLIT_LAUNCH.items() if any(tag in k and family_of(k) == fam for k in f)}
+    firsts = [(fam, first) for fam, first, second in FIRST_OF_TWO if any(second in k for k in f)]
     lines = [f"Scale factors from {COPY_KERNEL} ({copy_bytes / 2 ** 20:.0f} MiB read and written per dispatch): "
              f"FETCH_SIZE x {f_scale:.3f}, WRITE_SIZE x {w_scale:.3f}.", "",
              "| kernel | family | dispatches | FETCH_SIZE KiB/dispatch | WRITE_SIZE KiB/dispatch | HBM MiB/dispatch (scaled) |",
@@ -112,10 +112,8 @@ def traffic(fetch_csv, write_csv, copy_bytes=COPY_BYTES):
         fam = family_of(k)
         if fam:
             fams[fam] += b * len(f[k])
-            if fam in split:
-                if SPLIT_LAUNCH[fam] in k:
-                    launches[fam] += len(f[k])
-            elif fam not in SEQUENCES or FAMILIES[fam][0] in k:
+            first = any(fam == g and frag in k for g, frag in firsts)
+            if not first and (fam not in SEQUENCES or FAMILIES[fam][0] in k):
                 launches[fam] += len(f[k])
         lines.append(f"| `{k.replace('|', '/')[:130]}` | {fam or '-'} | {len(f[k])} | {fk:.1f} | {wk:.1f} | {b / 2 ** 20:.1f} |")
     record = {"sources_sha256": sources_sha256(), "fetch_scale": f_scale, "write_scale": w_scale,
