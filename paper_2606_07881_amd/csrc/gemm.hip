@@ -1487,7 +1487,16 @@ bool pipe_eligible(const GemmArgs& a) {
   auto covers = [](int64_t ld, int n) { return n % 8 == 0 || ld >= (n + 7) / 8 * 8; };
   const bool k_ok = a.K % 8 == 0 || (!AK && !BK) || (AK && !BK && a.a_zero_pad);
   return a.zeros != nullptr && al16(a.A) && al16(a.B) && al16(a.zeros) && k_ok && a.lda % 8 == 0 && a.ldb % 8 == 0 &&
-         a.lda < (1 << 22) && a.ldb < (1 << 22) && (AK || covers(a.lda, a.M)) && (BK || covers(a.ldb, a.N));
+         (AK || covers(a.lda, a.M)) && (BK || covers(a.ldb, a.N));
+}
+
+// The ping-pong kernel addresses a sub-tile by a 32-bit byte offset, up to 255
+// rows (K-major) or 31 lines (MN-major) from its base; the ring kernel's
+// addresses are 64-bit. Longer rows (a vocabulary or FFN width of 8M and more)
+// stay on the ring kernel.
+template <bool AK, bool BK>
+bool pp_reach(const GemmArgs& a) {
+  return a.lda < (AK ? 1 << 23 : 1 << 26) && a.ldb < (BK ? 1 << 23 : 1 << 26);
 }
 
 // Tiles and split-K count of a window weight gradient: long contractions over
@@ -1533,7 +1542,7 @@ hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
   if (a.seg_rows > 0) {
     // segmented B (the window weight gradients): ping-pong tiles, see gemm_window_splits
     if constexpr (sizeof(T) == 2 && !AK && !BK) {
-      if (pipe_eligible<AK, BK>(a) && a.seg_rows % 64 == 0 && a.seg_count >= 1 && a.seg_first >= 0)
+      if (pipe_eligible<AK, BK>(a) && pp_reach<AK, BK>(a) && a.seg_rows % 64 == 0 && a.seg_count >= 1 && a.seg_first >= 0)
         return window_plan(a.M, a.N, a.K).bn == 256 ? launch_pp<TO, AK, BK, EPI, 256>(a, splits, st)
                                                     : launch_pp<TO, AK, BK, EPI, 128>(a, splits, st);
     }
@@ -1571,7 +1580,7 @@ hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
       if constexpr (AK && BK && sizeof(TO) == 2) {
         const int64_t tm = (a.M + 255) / 256, cus = cu_count();
         auto rounds = [&](int64_t n, int bn) { return (double)((tm * ((n + bn - 1) / bn) + cus - 1) / cus); };
-        if (splits == 1) {
+        if (splits == 1 && pp_reach<AK, BK>(a)) {
           const double wide = 1.8 * rounds(a.N, 256), narrow = rounds(a.N, 128);
           // Columns of whole 256 x 256 rounds, the others in a launch of their own:
           // 8192 x 3072 as 2048 + 1024, at K 1024 qkv 67 -> 36.9 + 23.4 us; at K
@@ -1600,7 +1609,9 @@ hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
       // 256 x 128 ping-pong tiles, whose partial last k-tile does not slow
       // the others (8192 x 1024 x 50257: 1115 us on the register-staged
       // kernel, 690 now).
-      if constexpr (AK && !BK && EPI == EPI_STORE) return launch_pp<TO, AK, BK, EPI, 128>(a, splits, st);
+      if constexpr (AK && !BK && EPI == EPI_STORE) {
+        if (pp_reach<AK, BK>(a)) return launch_pp<TO, AK, BK, EPI, 128>(a, splits, st);
+      }
       if constexpr (!AK || EPI == EPI_GELU_GRAD) return launch_pipe<TO, AK, BK, EPI, P128x128o2>(a, splits, st);
       else return launch_pipe<TO, AK, BK, EPI, P256x128>(a, splits, st);
     }
@@ -1831,7 +1842,7 @@ hipError_t gemm_wgrad(DType dt, const GemmArgs& a, hipStream_t st) {
   // round would leave most CUs idle for as long as a full one. The 50257 x 1024
   // LM head over 8192 rows: 1453 us on the register-staged 128 x 128 kernel,
   // 625 (3 rounds) + 50 us now.
-  if (dt == DT_BF16 && pipe_eligible<false, false>(a)) {
+  if (dt == DT_BF16 && pipe_eligible<false, false>(a) && pp_reach<false, false>(a)) {
     const int cus = cu_count(), tn = (a.N + 255) / 256, tm = a.M / 256;
     const int rows_t = tn <= cus ? tm * tn / cus * cus / tn : 0;   // row tiles of the whole rounds
     if (rows_t > 0) {
