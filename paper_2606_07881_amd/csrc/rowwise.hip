@@ -523,7 +523,7 @@ __global__ void __launch_bounds__(NT) ce_bwd_kernel(const float* __restrict__ z,
     float g[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j)   // columns V .. ldz - 1 (whatever they hold): zero
-      g[j] = v + j < V ? scale * (fast_exp(q[j >> 2][j & 3] - l) - (v + j == y ? 1.f : 0.f)) : 0.f;
+      g[j] = v + j < V ? scale * (expf(q[j >> 2][j & 3] - l) - (v + j == y ? 1.f : 0.f)) : 0.f;
     if constexpr (sizeof(T) == 2) {
       st16(dr + v, pack_vec<T>(g));
     } else {
