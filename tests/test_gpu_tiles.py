@@ -101,3 +101,13 @@ def test_dropout_draws(binding, dh, seq):  # noqa: F811
 @pytest.mark.parametrize("dh", [32, 64, 128])
 def test_attention_large_grid(binding, dh, name):  # noqa: F811
     _check(binding, small_cfg(name, n_layers=1, d_model=4 * dh, n_heads=4, head_dim=dh, d_ff=64, seq=300, micro_batch=30))
+
+
+# embeddings: one 8-column chunk per lane with idle lanes, two steps of 512
+# columns with a partial last one, more than one workgroup of columns and a
+# partial one, the last token's workgroup partly idle; one sequence, 8 and 9
+# (a second step of loads); ids repeat
+@pytest.mark.parametrize("name", ["first_bf16", "first_fp32"])
+@pytest.mark.parametrize("d,seq,mu", [(32, 1, 1), (288, 37, 8), (544, 21, 9)])
+def test_embeddings(binding, name, d, seq, mu):  # noqa: F811
+    _check(binding, small_cfg(name, d_model=d, n_heads=d // 32, head_dim=32, d_ff=64, seq=seq, micro_batch=mu))
