@@ -41,8 +41,15 @@ namespace {
 constexpr int KVN = 8, GROUP_M = 8;
 
 // Tile configuration: a BM x BN output tile per workgroup, WM x WN per wavefront.
-template <int BM_, int BN_, int WM_, int WN_>
+// CH partial sums per output (an MFMA adds to every CH-th): the k-ranges of the
+// small fp32 tiles are split over fewer workgroups than those of 128 x 128 ones,
+// and in one chain their weight gradients were 13-30% further from a 64-bit
+// product than on split 128 x 128 tiles (256-wide block, 600 tokens: 4.0e-7 with
+// the splits, 4.5e-7 in one chain, 2.5e-7 in four; the block's output 8.1e-8,
+// 8.1e-8, 5.2e-8). The MFMAs issue at the same rate either way.
+template <int BM_, int BN_, int WM_, int WN_, int CH_ = 1>
 struct Tile {
+  static constexpr int CH = CH_;
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
   static constexpr int WAVES = (BM / WM) * (BN / WN);
   static constexpr int NT = 64 * WAVES;
@@ -258,11 +265,14 @@ __global__ void __launch_bounds__(CF::NT, 1) gemm_kernel(GemmArgs a, int k_per_s
   // fp32 MN-major operands load V x V blocks on part of the threads; spread A and B apart
   const int tid_b = (!AK && !BK && sizeof(T) == 4) ? ((tid + NT / 2) % NT) : tid;
 
-  floatx4 acc[WM / 16][WN / 16];
+  constexpr int CH = CF::CH;
+  floatx4 acc[CH][WM / 16][WN / 16];
 #pragma unroll
-  for (int i = 0; i < WM / 16; ++i)
+  for (int c = 0; c < CH; ++c)
 #pragma unroll
-    for (int j = 0; j < WN / 16; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < WM / 16; ++i)
+#pragma unroll
+      for (int j = 0; j < WN / 16; ++j) acc[c][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   if (nk > 0) {
     la.load(A, a.lda, m0, a.M, k_begin, k_end, tid);
@@ -290,7 +300,13 @@ __global__ void __launch_bounds__(CF::NT, 1) gemm_kernel(GemmArgs a, int k_per_s
 #pragma unroll
       for (int i = 0; i < WM / 16; ++i)
 #pragma unroll
-        for (int j = 0; j < WN / 16; ++j) mma_step<T>(acc[i][j], xf[j], yf[i]);
+        for (int j = 0; j < WN / 16; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const uint32_t xw = xf[j][q], yw = yf[i][q];
+            floatx4& c = acc[q % CH][i][j];
+            c = __builtin_amdgcn_mfma_f32_16x16x4f32(as_float(xw), as_float(yw), c, 0, 0, 0);
+          }
     }
     if (kt + 1 < nk) {
       la.store(smem[cur ^ 1], tid);
@@ -302,8 +318,13 @@ __global__ void __launch_bounds__(CF::NT, 1) gemm_kernel(GemmArgs a, int k_per_s
 #pragma unroll
   for (int i = 0; i < WM / 16; ++i)
 #pragma unroll
-    for (int j = 0; j < WN / 16; ++j)
-      epilogue<T, TO, EPI>(a, m0 + wm0 + i * 16 + (l & 15), n0 + wn0 + j * 16 + 4 * (l >> 4), acc[i][j]);
+    for (int j = 0; j < WN / 16; ++j) {
+#pragma unroll
+      for (int h = CH / 2; h > 0; h /= 2)
+#pragma unroll
+        for (int c = 0; c < h; ++c) acc[c][i][j] += acc[c + h][i][j];
+      epilogue<T, TO, EPI>(a, m0 + wm0 + i * 16 + (l & 15), n0 + wn0 + j * 16 + 4 * (l >> 4), acc[0][i][j]);
+    }
 }
 
 // ============================================================================================
@@ -1428,8 +1449,8 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_kernel(GemmArgs a, int k_per_s
 
 // Tile configurations; the choice per call is made in launch().
 typedef Tile<128, 128, 64, 64> T128x128;
-typedef Tile<64, 64, 32, 32> T64x64;
-typedef Tile<32, 32, 16, 16> T32x32;
+typedef Tile<64, 64, 32, 32, 4> T64x64;
+typedef Tile<32, 32, 16, 16, 4> T32x32;
 
 typedef PipeTile<256, 128, 64, 64, 3> P256x128;
 typedef PipeTile<128, 128, 64, 64, 2, 2> P128x128o2;   // two workgroups per CU
