@@ -622,6 +622,9 @@ __device__ __forceinline__ void ce_stats_panel(const GemmArgs& a, const float* c
     const int nv = min(64, a.N - nb);
     const float* row = cl + r * LDC + 64 * g;
     float mx = -INFINITY, sum = 0.f;
+    // The sum is of exp(x - ref): a group of nothing but -inf has no finite maximum
+    // to subtract, and sums to 0. (A NaN still makes the sum NaN.)
+    auto ref_of = [](float m) { return m == -INFINITY ? 0.f : m; };
     if (nv == 64) {
       floatx4 v[16];
 #pragma unroll
@@ -629,13 +632,15 @@ __device__ __forceinline__ void ce_stats_panel(const GemmArgs& a, const float* c
         v[c] = *reinterpret_cast<const floatx4*>(row + 4 * c);
         mx = fmaxf(fmaxf(mx, fmaxf(v[c][0], v[c][1])), fmaxf(v[c][2], v[c][3]));
       }
+      const float ref = ref_of(mx);
 #pragma unroll
       for (int c = 0; c < 16; ++c)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) sum += fast_exp(v[c][j] - mx);
+        for (int j = 0; j < 4; ++j) sum += fast_exp(v[c][j] - ref);
     } else {
       for (int c = 0; c < nv; ++c) mx = fmaxf(mx, row[c]);
-      for (int c = 0; c < nv; ++c) sum += fast_exp(row[c] - mx);
+      const float ref = ref_of(mx);
+      for (int c = 0; c < nv; ++c) sum += fast_exp(row[c] - ref);
     }
     const int64_t q = (int64_t)m * a.ld_part + nb / 64;
     *reinterpret_cast<float2*>(a.ce_part + 2 * q) = make_float2(mx, sum);

@@ -37,7 +37,7 @@ enum GemmLayout { GEMM_NT = 0, GEMM_NN = 1, GEMM_TN = 2 };
 // Softmax cross-entropy over the output columns (bf16 GEMM_NT only, one split):
 //   EPI_CE_STATS   nothing stored in C; per row m and 64-column group g (columns
 //                  64g .. 64g+63 below N): ce_part[2 (m ld_part + g) + {0, 1}] =
-//                  {max, sum exp(acc - max)}; ce_zt[m] = acc at column row_tgt[m]
+//                  {max, sum exp(acc - max)}, {-inf, 0} if all are -inf; ce_zt[m] = acc at column row_tgt[m]
 //   EPI_STORE_CE   C = acc (fp32) and the statistics of EPI_CE_STATS
 //   EPI_CE_GRAD    C = alpha * (exp(acc - row_lse[m]) - [n == row_tgt[m]])  (bf16)
 enum GemmEpi { EPI_STORE = 0, EPI_BIAS, EPI_BIAS_RES, EPI_BIAS_GELU, EPI_GELU_GRAD, EPI_ACC, EPI_ATOMIC, EPI_CE_STATS,
