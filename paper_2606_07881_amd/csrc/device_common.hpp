@@ -273,11 +273,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // (exp2f adds a rescaling sequence around it to return denormals).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// e^x for x <= 0 differences of logits: one multiplication and the hardware
-// exponential. The argument's rounding is 2^-24 |x| log2 e, so terms that count
-// in a sum (x > -17) are good to 2 ulp.
-__device__ __forceinline__ float fast_exp(float x) { return fast_exp2(x * 1.4426950408889634f); }
-
 // Sum over the 16 lanes of a DPP row (lanes 16k .. 16k + 15), returned to every
 // lane of the row: data-parallel moves within the row (swap neighbours, swap
 // pairs, reverse each half row, reverse the row) with no LDS traffic.

@@ -548,7 +548,7 @@ __device__ __forceinline__ void staged_out(const GemmArgs& a, const float* cl, i
       const float l = a.row_lse[m];
       const int y = a.row_tgt[m] - n;
 #pragma unroll
-      for (int j = 0; j < U; ++j) o[j] = a.alpha * (fast_exp(o[j] - l) - (j == y ? 1.f : 0.f));
+      for (int j = 0; j < U; ++j) o[j] = a.alpha * (expf(o[j] - l) - (j == y ? 1.f : 0.f));
     } else {
 #pragma unroll
       for (int j = 0; j < U; ++j) {
@@ -636,11 +636,11 @@ __device__ __forceinline__ void ce_stats_panel(const GemmArgs& a, const float* c
 #pragma unroll
       for (int c = 0; c < 16; ++c)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) sum += fast_exp(v[c][j] - ref);
+        for (int j = 0; j < 4; ++j) sum += expf(v[c][j] - ref);
     } else {
       for (int c = 0; c < nv; ++c) mx = fmaxf(mx, row[c]);
       const float ref = ref_of(mx);
-      for (int c = 0; c < nv; ++c) sum += fast_exp(row[c] - ref);
+      for (int c = 0; c < nv; ++c) sum += expf(row[c] - ref);
     }
     const int64_t q = (int64_t)m * a.ld_part + nb / 64;
     *reinterpret_cast<float2*>(a.ce_part + 2 * q) = make_float2(mx, sum);
@@ -1692,9 +1692,11 @@ hipError_t by_layout(bool out_f32, GemmLayout lay, GemmEpi epi, const GemmArgs& 
     if constexpr (sizeof(T) == 2) {
       if (lay != GEMM_NT || !pipe_eligible<true, true>(a) || a.row_tgt == nullptr || a.colsum != nullptr)
         return hipErrorInvalidValue;
-      // 256 x 256 ping-pong tiles (8192 x 50257 x 1024: 1120 us storing fp32 logits on 256 x 128
-      // ring tiles, 1015 with the statistics, which save a 953 us pass over the logits; without
-      // logits 1085 -> 750 and 1200 -> 880 us)
+      // 256 x 256 ping-pong tiles (8192 x 50257 x 1024: 1111 us storing fp32 logits on 256 x 128
+      // ring tiles, 1115 with the statistics, which save a 950 us pass over the logits; without
+      // logits 1079 -> 871 and 1203 -> 978 us). About 100 us of each are the exponentials: with a
+      // once-rounded argument 2^(x log2 e) they took 1015, 736 and 872 us, but were off by up to
+      // |x| 2^-24 where expf is good to an ulp.
       if (epi != EPI_CE_GRAD) {
         if (a.ce_part == nullptr || a.ce_zt == nullptr || a.ld_part < (a.N + 63) / 64) return hipErrorInvalidValue;
         if (epi == EPI_STORE_CE) return launch_pp<float, true, true, EPI_STORE_CE, 256>(a, 1, st);

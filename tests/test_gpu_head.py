@@ -46,3 +46,38 @@ def test_minus_infinity_logits(binding, dead, fused):  # noqa: F811
     for n in ("w_lm", "lnf_b"):
         assert rel_err(G[n], o_G[n]) <= tol(c, "grad"), n
     assert not np.any(G["w_lm"][dead[0]:dead[1]])
+
+
+def _bf16_rne(x):
+    m, e = np.frexp(x)   # 8 significant bits
+    return np.ldexp(np.rint(m * 256) / 256, e)
+
+
+# The logit gradient of one token, exp(z) / 2 in bf16, at logits z between -80 and -24 whose
+# gradient lies 2^-22 to 2^-20 from a rounding boundary. An exponential within one ulp (2^-23)
+# rounds every one of them correctly; one whose argument is first multiplied by log2 e and
+# rounded is off by up to |z| 2^-24 and gets about a quarter of them wrong. The loss is log(1 + 2e-9):
+# z - lse rounds to z.
+@pytest.mark.parametrize("fused", [0, 1])
+def test_logit_gradient_exponential(binding, fused):  # noqa: F811
+    a, b = np.meshgrid(-(24.0 + np.arange(56 * 2) / 2), np.arange(128 * 16) / 4096, indexing="ij")
+    z = (a + b).ravel()
+    g = 0.5 * np.exp(z)
+    m = np.frexp(g)[0] * 256
+    off = np.abs(m - np.floor(m) - 0.5) / m   # relative distance from the nearest boundary
+    pick = np.flatnonzero((off > 2.0 ** -22) & (off < 2.0 ** -20))
+    assert pick.size >= 50
+    V = 1 + pick.size
+    c = small_cfg("last_bf16", vocab=V, d_model=64, n_heads=1, head_dim=64, d_ff=64, seq=1, micro_batch=1,
+                  fused_head=fused)
+    inp = Inputs(c, 0, 1)
+    p = inp.params
+    p["lnf_g"][:], p["lnf_b"][:], p["w_lm"][:] = 0.0, 0.0, 0.0
+    p["lnf_b"][:3] = 1.0, 2.0 ** -8, 2.0 ** -12
+    ai, bi = np.divmod(pick, 128 * 16)
+    p["w_lm"][1:, 0] = -(24.0 + ai / 2)   # each exact in bf16, and so are their products' sum in fp32
+    p["w_lm"][1:, 1] = bi // 16
+    p["w_lm"][1:, 2] = bi % 16
+    inp.tgt[0][:] = 0   # logit 0
+    _, _, G = _pair(binding, c, inp)
+    np.testing.assert_array_equal(G["w_lm"][1:, 0], _bf16_rne(g[pick]))
