@@ -36,6 +36,32 @@ int cu_count() {
   return cus;
 }
 
+// fp32 products with a K-major A (forward, input gradients): 128 x 128 tiles when
+// their rounds over the CUs are at least 7/8 full, else 64 x 64, and 32 x 32 when
+// those are fewer than two per CU. A 32-deep k-tile of matrix work is 2.4, 0.7 and
+// 0.45 us at edge 128, 64 and 32 (the last two bound by the latency of the loads),
+// so 64 x 64 tiles do the same work at 1.1 to 1.2 of the time of full rounds and
+// win by sharing a partial one. us on 128 / 64 / 32 at K 512, NT and NN, by tiles of
+// 128 x 128: 256 of them 49 / 53 / 52 and 48 / 54 / 64; 384 78 / 67 / 75 and
+// 80 / 73 / 90; 448 78 / 78 / 86 and 80 / 87 / 105; 544 120 / 96 / 103 and
+// 120 / 105 / 125. A 256 x 128 product over 512 runs two 128 x 128 tiles on the
+// whole chip, or 32 of 32 x 32: 33 -> 8.4 us.
+// A single round over a short K costs its first loads and its epilogue: below K 256
+// the forward products (GEMM_NT) take 64 x 64 there too (256 tiles of 128 x 128, K 64
+// and 128: 14.1 / 13.2, 19.0 / 18.6; K 256 28.9 / 30.3), not the input gradients
+// (GEMM_NN: 11.9 / 13.9, 17.2 / 20.8).
+// Weight gradients (GEMM_TN) split K over idle CUs: the largest edge that gives two
+// workgroups per CU (2048 x 512 over 8192 rows 241 / 204 / 261, 1024 x 1024 over
+// 4096 170 / 115 / 134, 4096 x 1024 370 / 366 / 515).
+int gemm_f32_tile(GemmLayout lay, int M, int N, int K, int splits) {
+  const int64_t cus = cu_count();
+  auto tiles = [&](int e) { return (int64_t)((M + e - 1) / e) * ((N + e - 1) / e) * splits; };
+  const int64_t t = tiles(128), rounds = (t + cus - 1) / cus;
+  const bool brief = lay == GEMM_NT && rounds == 1 && K < 256;
+  if (lay == GEMM_TN ? t >= 2 * cus : 8 * t >= 7 * rounds * cus && !brief) return 128;
+  return tiles(64) >= 2 * cus ? 64 : 32;
+}
+
 namespace {
 
 constexpr int KVN = 8, GROUP_M = 8;
@@ -1552,17 +1578,6 @@ WindowPlan window_plan(int M, int N, int64_t K) {
   return best;
 }
 
-// fp32 products: the largest tile edge that still gives two workgroups per CU,
-// else the smallest. A 256 x 128 product over 512 runs two 128 x 128 tiles on
-// the whole chip, or 32 of 32 x 32: 33 -> 8.4 us a launch over its calls with
-// K 128 and 512 (matrix work is 2.4, 0.7 and 0.45 us per 32-deep k-tile at 128,
-// 64 and 32, the last two bound by the latency of the loads).
-int f32_tile(int M, int N, int splits) {
-  for (int e = 128; e > 32; e /= 2)
-    if ((int64_t)((M + e - 1) / e) * ((N + e - 1) / e) * splits >= 2 * cu_count()) return e;
-  return 32;
-}
-
 template <typename T, typename TO, bool AK, bool BK, int EPI>
 hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
   if (a.seg_rows > 0) {
@@ -1644,7 +1659,7 @@ hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
   }
   hipError_t e;
   if constexpr (sizeof(T) == 4) {
-    switch (f32_tile(a.M, a.N, splits)) {
+    switch (gemm_f32_tile(AK ? (BK ? GEMM_NT : GEMM_NN) : GEMM_TN, a.M, a.N, a.K, splits)) {
       case 32: e = launch_cf<T, TO, AK, BK, EPI, T32x32>(a, splits, st); break;
       case 64: e = launch_cf<T, TO, AK, BK, EPI, T64x64>(a, splits, st); break;
       default: e = launch_cf<T, TO, AK, BK, EPI, T128x128>(a, splits, st); break;
@@ -1854,7 +1869,7 @@ int gemm_acc_splits(DType dt, int M, int N, int K) {
   const int kt = (K + 31) / 32;
   return best_of([&](int sp) {
     if (sp > kt) return 1e30;
-    const int e = f32_tile(M, N, sp);
+    const int e = gemm_f32_tile(GEMM_TN, M, N, K, sp);
     const double tiles = (double)((M + e - 1) / e) * ((N + e - 1) / e), t_k = e == 128 ? 2.4 : e == 64 ? 0.7 : 0.45;
     return std::ceil(tiles * sp / (2 * cu_count())) * std::ceil((double)kt / sp) * t_k;
   });

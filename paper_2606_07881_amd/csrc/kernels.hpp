@@ -119,6 +119,8 @@ hipError_t gemm_wgrad(DType dt, const GemmArgs& a, hipStream_t st);
 // dtype: element type of A, B, aux and of C/C2 unless out_f32 (then C is float).
 // splits > 1 is only valid with EPI_ATOMIC.
 hipError_t gemm(DType dt, bool out_f32, GemmLayout lay, GemmEpi epi, const GemmArgs& a, int splits, hipStream_t st);
+// Tile edge (128, 64 or 32) of an fp32 product.
+int gemm_f32_tile(GemmLayout lay, int M, int N, int K, int splits);
 // Split-K count of a window weight gradient (GEMM_TN, segmented B) over K rows.
 int gemm_window_splits(int M, int N, int64_t K);
 
