@@ -62,6 +62,65 @@ int gemm_f32_tile(GemmLayout lay, int M, int N, int K, int splits) {
   return tiles(64) >= 2 * cus ? 64 : 32;
 }
 
+// Products with both operands K-major, by the rounds their tiles take on the CUs.
+// Grids that leave CUs idle: the largest tiles that still fit one round. A
+// k-tile takes about 0.2 us on 64 x 64 tiles, 0.24 on 128 x 64, 0.36 on
+// 128 x 128 and 0.6-0.8 on 256 x 128, so below one round of tiles the
+// smaller ones win (128 x 768 x 3072: 34.1 us on 256 x 128, 12.8 on 64 x
+// 64; 2048 x 768 x 3072: 36.9, 21.9 on 384 of 64 x 64, 18.3 on 192 of 128
+// x 64; 4096 x 1024 x 4096: 48.8, 54.4, 49.1, 38.5 on 256 of 128 x 128),
+// above it the larger ones, which re-read the operands less.
+// 256 x 256 ping-pong tiles where they take fewer rounds than 256 x 128 ring
+// tiles, a round of them costing 1.8 of the others (whole rounds at 8192 x 4096
+// x 1024, in the stage: FFN1 forward 106 -> 88.9 us, FFN2 input gradient 110 ->
+// 82.2; at 8192 x 2048, mean of K 2048 and 8192: residual 163 -> 131, plain 157
+// -> 131; qkv 8192 x 6144 x 2048: 209 -> 170).
+// Columns of whole 256 x 256 rounds, the others in a launch of their own: 8192 x
+// 3072 as 2048 + 1024, at K 1024 qkv 67 -> 36.9 + 23.4 us; at K 768 FFN1 forward
+// 68.6 -> 39.3 + 24.4, FFN2 input gradient 65 -> 36.4 + 25.0; qkv 8192 x 2304 x
+// 768 (2048 + 256) 54.5 -> 29.9 + 9.5.
+// The rest: 256 x 128 ring tiles, which re-read the weights half as often as
+// 128 x 128 ones.
+KmajorPlan gemm_kmajor_plan(int M, int N) {
+  const int64_t cus = cu_count(), tm = (M + 255) / 256;
+  auto tiles = [&](int bm, int bn) { return (int64_t)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  if (tiles(64, 64) <= cus) return {KT_64x64, 0};
+  if (tiles(128, 64) <= cus) return {KT_128x64, 0};
+  if (tiles(128, 128) <= cus) return {KT_128x128, 0};
+  auto rounds = [&](int64_t n, int bn) { return (double)((tm * ((n + bn - 1) / bn) + cus - 1) / cus); };
+  const double wide = 1.8 * rounds(N, 256), narrow = rounds(N, 128);
+  const int64_t per = cus % tm == 0 ? cus / tm * 256 : 0, n1 = per > 0 ? N / per * per : 0;
+  if (n1 > 0 && n1 < N && 1.8 * rounds(n1, 256) + rounds(N - n1, 128) + 0.1 < std::min(wide, narrow))
+    return {KT_PP_256x256, (int)n1};
+  return {wide < narrow ? KT_PP_256x256 : KT_256x128, 0};
+}
+
+// Tiles and split-K count of a window weight gradient: long contractions over
+// few output tiles, so K is split until one round of workgroups (the CUs) is
+// full, each split at least 512 rows, and of the two tile widths the one with
+// the least work per CU is taken, a 256 x 256 tile costing 1.8 of 256 x 128.
+// Atomic adds grow with the splits, at most 32. At 768-wide blocks over 32768
+// rows: 3072 x 768 in 207 us with the three-stage ring on 256 x 128 tiles (two
+// rounds), 196 ping-pong, 172 on 252 of 256 x 256; 2304 x 768 170, 160, 138; 768
+// x 768 114, 112, 93. About 60 us of each are the atomic adds, which cross the
+// XCDs in memory.
+WindowPlan gemm_window_plan(int M, int N, int64_t K) {
+  WindowPlan best{128, 1};
+  double best_t = 1e30;
+  const int cus = cu_count();
+  for (int bn : {256, 128}) {
+    const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + bn - 1) / bn), kt = (K + 63) / 64;
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(32, K / 512));
+    const int sp = (int)std::max<int64_t>(1, std::min(most, cus / tiles));
+    const double t = (double)((tiles * sp + cus - 1) / cus) * (double)((kt + sp - 1) / sp) * (bn == 256 ? 1.8 : 1.0);
+    if (t < best_t) {
+      best_t = t;
+      best = {bn, sp};
+    }
+  }
+  return best;
+}
+
 namespace {
 
 constexpr int KVN = 8, GROUP_M = 8;
@@ -84,18 +143,17 @@ struct Tile {
 // Register-staged tile loader (global -> registers -> LDS), fp32. K-major
 // operands are copied as 16-byte vectors, MN-major ones loaded as 4 x 4 blocks
 // and transposed in registers.
-template <typename T, int ROWS, bool KMAJ, int NT>
+template <int ROWS, bool KMAJ, int NT>
 struct TileLoader {
-  static_assert(sizeof(T) == 4, "bf16 products take the direct-to-LDS kernels");
-  static constexpr int V = Vec<T>::V;
+  static constexpr int V = Vec<float>::V;
   static constexpr int ITEMS = KMAJ ? ROWS * KVN : (ROWS / V) * KVN;
   static constexpr int PT = (ITEMS + NT - 1) / NT;
   static constexpr int NV = KMAJ ? 1 : V;
   u32x4 r[PT][NV];
 
   // rows [row0, row0+ROWS) of `rows_total`; contracted [k0, k0 + 8V) of k_end.
-  __device__ __forceinline__ void load(const T* src, int64_t ld, int row0, int rows_total, int k0, int k_end,
-                                       int tid) {
+  __device__ __forceinline__ void load(const float* src, int64_t ld, int row0, int rows_total, int k0,
+                                       int k_end, int tid) {
 #pragma unroll
     for (int p = 0; p < PT; ++p) {
       const int it = tid + p * NT;
@@ -106,7 +164,7 @@ struct TileLoader {
         u32x4 v = {0, 0, 0, 0};
         if (row < rows_total && k < k_end) {
           v = ld16(src + (int64_t)row * ld + k);
-          if (k + V > k_end) v = vmask_tail<T>(v, k_end - k);
+          if (k + V > k_end) v = vmask_tail<float>(v, k_end - k);
         }
         r[p][0] = v;
       } else {
@@ -118,7 +176,7 @@ struct TileLoader {
           u32x4 v = {0, 0, 0, 0};
           if (k < k_end && rb < rows_total) {
             v = ld16(src + (int64_t)k * ld + rb);
-            if (rb + V > rows_total) v = vmask_tail<T>(v, rows_total - rb);
+            if (rb + V > rows_total) v = vmask_tail<float>(v, rows_total - rb);
           }
           r[p][j] = v;
         }
@@ -137,7 +195,7 @@ struct TileLoader {
       } else {
         const int kv = it % KVN, rr = it / KVN;
         u32x4 out[V];
-        transpose_block<T>(r[p], out);
+        transpose_block<float>(r[p], out);
 #pragma unroll
         for (int i = 0; i < V; ++i) tile[lds_slot<ROWS>(kv, rr * V + i)] = out[i];
       }
@@ -172,74 +230,55 @@ __device__ __forceinline__ void gelu_and_grad(float u, float& g, float& dg) {
   dg = gelu_grad_s(u, u2, sg);
 }
 
-// Four consecutive elements [i, i+4) of a T array as floats (one 8- or 16-byte load).
-template <typename T> __device__ __forceinline__ void ld4f(const void* p, int64_t i, float* out) {
-  const T* q = reinterpret_cast<const T*>(p) + i;
-  if (sizeof(T) == 4) {
-    const u32x4 v = ld16(q);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) out[j] = vget<float>(v, j);
-  } else {
-    const u32x2 v = *reinterpret_cast<const u32x2*>(q);
-    const u32x4 w = {v[0], v[1], 0u, 0u};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) out[j] = vget<bf16>(w, j);
-  }
-}
-template <typename T> __device__ __forceinline__ float ldf(const void* p, int64_t i) {
-  return to_f32(reinterpret_cast<const T*>(p)[i]);
-}
-
 // Write four consecutive outputs C[m][n .. n+3].
-template <typename TO>
-__device__ __forceinline__ void store4(TO* C, int64_t idx, const float* v, int nvalid) {
-  if (nvalid >= 4) {
-    if (sizeof(TO) == 4) {
-      st16(C + idx, u32x4{__builtin_bit_cast(uint32_t, v[0]), __builtin_bit_cast(uint32_t, v[1]),
-                          __builtin_bit_cast(uint32_t, v[2]), __builtin_bit_cast(uint32_t, v[3])});
-    } else {
-      *reinterpret_cast<u32x2*>(C + idx) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-    }
-  } else {
-    for (int j = 0; j < nvalid; ++j) C[idx + j] = from_f32<TO>(v[j]);
-  }
+__device__ __forceinline__ void store4(float* C, int64_t idx, const float* v, int nvalid) {
+  if (nvalid >= 4)
+    st16(C + idx, u32x4{__builtin_bit_cast(uint32_t, v[0]), __builtin_bit_cast(uint32_t, v[1]),
+                        __builtin_bit_cast(uint32_t, v[2]), __builtin_bit_cast(uint32_t, v[3])});
+  else
+    for (int j = 0; j < nvalid; ++j) C[idx + j] = v[j];
 }
 
-template <typename T, typename TO, int EPI>
+template <int EPI>
 __device__ __forceinline__ void epilogue(const GemmArgs& a, int m, int n, const floatx4& acc) {
   if (m >= a.M || n >= a.N) return;
   const int nv = min(4, a.N - n);
-  if (EPI == EPI_ACC || EPI == EPI_ATOMIC) {
-    float* C = reinterpret_cast<float*>(a.C) + (int64_t)m * a.ldc + n;
-    if (EPI == EPI_ATOMIC) {
-      for (int j = 0; j < nv; ++j) atomicAdd(C + j, acc[j]);
-    } else if (nv == 4) {
-      u32x4 old = ld16(C);
+  float* C = reinterpret_cast<float*>(a.C);
+  const int64_t at = (int64_t)m * a.ldc + n;
+  if (EPI == EPI_ATOMIC) {
+    for (int j = 0; j < nv; ++j) atomicAdd(C + at + j, acc[j]);
+    return;
+  }
+  if (EPI == EPI_ACC) {
+    if (nv == 4) {
+      const u32x4 old = ld16(C + at);
       float o[4];
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t w = old[j];
-        o[j] = as_float(w) + acc[j];
-      }
-      store4<float>(reinterpret_cast<float*>(a.C), (int64_t)m * a.ldc + n, o, 4);
+      for (int j = 0; j < 4; ++j) o[j] = vget<float>(old, j) + acc[j];
+      store4(C, at, o, 4);
     } else {
-      for (int j = 0; j < nv; ++j) C[j] += acc[j];
+      for (int j = 0; j < nv; ++j) C[at + j] += acc[j];
     }
     return;
   }
   float o[4], bias[4] = {0.f, 0.f, 0.f, 0.f}, aux[4] = {0.f, 0.f, 0.f, 0.f};
   constexpr bool HAS_BIAS = EPI == EPI_BIAS || EPI == EPI_BIAS_RES || EPI == EPI_BIAS_GELU;
   constexpr bool HAS_AUX = EPI == EPI_BIAS_RES || EPI == EPI_GELU_GRAD;
+  const float* ap = reinterpret_cast<const float*>(a.aux) + (int64_t)m * a.ld_aux + n;
   if (nv == 4) {
     if (HAS_BIAS) {
       const u32x4 b = ld16(a.bias + n);
 #pragma unroll
       for (int j = 0; j < 4; ++j) bias[j] = vget<float>(b, j);
     }
-    if (HAS_AUX) ld4f<T>(a.aux, (int64_t)m * a.ld_aux + n, aux);
+    if (HAS_AUX) {
+      const u32x4 x = ld16(ap);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) aux[j] = vget<float>(x, j);
+    }
   } else {
     for (int j = 0; j < nv; ++j) {
       if (HAS_BIAS) bias[j] = a.bias[n + j];
-      if (HAS_AUX) aux[j] = ldf<T>(a.aux, (int64_t)m * a.ld_aux + n + j);
+      if (HAS_AUX) aux[j] = ap[j];
     }
   }
   float g[4];
@@ -251,8 +290,8 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, int m, int n, const 
     if (EPI == EPI_BIAS_GELU) gelu_and_grad(x, g[j], x);
     o[j] = x;
   }
-  store4<TO>(reinterpret_cast<TO*>(a.C), (int64_t)m * a.ldc + n, o, nv);
-  if (EPI == EPI_BIAS_GELU) store4<TO>(reinterpret_cast<TO*>(a.C2), (int64_t)m * a.ldc + n, g, nv);
+  store4(C, at, o, nv);
+  if (EPI == EPI_BIAS_GELU) store4(reinterpret_cast<float*>(a.C2), at, g, nv);
 }
 
 __device__ __forceinline__ void tile_coords(int pid, int tiles_m, int tiles_n, int& tm, int& tn) {
@@ -267,11 +306,11 @@ __device__ __forceinline__ void tile_coords(int pid, int tiles_m, int tiles_n, i
   tn = in_group / gm;
 }
 
-template <typename T, typename TO, bool AK, bool BK, int EPI, class CF>
+template <bool AK, bool BK, int EPI, class CF>
 __global__ void __launch_bounds__(CF::NT, 1) gemm_kernel(GemmArgs a, int k_per_split) {
   constexpr int BM = CF::BM, BN = CF::BN, WM = CF::WM, WN = CF::WN, NT = CF::NT;
   constexpr int WAVES_N = BN / WN;
-  constexpr int V = Vec<T>::V;
+  constexpr int V = Vec<float>::V;
   constexpr int BKE = KVN * V;
   __shared__ u32x4 smem[2][(BM + BN) * KVN];
   const int tid = threadIdx.x, l = lane_id(), w = tid >> 6;
@@ -284,12 +323,12 @@ __global__ void __launch_bounds__(CF::NT, 1) gemm_kernel(GemmArgs a, int k_per_s
   const int nk = (k_end - k_begin + BKE - 1) / BKE;
   const int wm0 = (w / WAVES_N) * WM, wn0 = (w % WAVES_N) * WN;
 
-  const T* A = reinterpret_cast<const T*>(a.A);
-  const T* B = reinterpret_cast<const T*>(a.B);
-  TileLoader<T, BM, AK, NT> la;
-  TileLoader<T, BN, BK, NT> lb;
-  // fp32 MN-major operands load V x V blocks on part of the threads; spread A and B apart
-  const int tid_b = (!AK && !BK && sizeof(T) == 4) ? ((tid + NT / 2) % NT) : tid;
+  const float* A = reinterpret_cast<const float*>(a.A);
+  const float* B = reinterpret_cast<const float*>(a.B);
+  TileLoader<BM, AK, NT> la;
+  TileLoader<BN, BK, NT> lb;
+  // MN-major operands load V x V blocks on part of the threads; spread A and B apart
+  const int tid_b = (!AK && !BK) ? ((tid + NT / 2) % NT) : tid;
 
   constexpr int CH = CF::CH;
   floatx4 acc[CH][WM / 16][WN / 16];
@@ -320,9 +359,9 @@ __global__ void __launch_bounds__(CF::NT, 1) gemm_kernel(GemmArgs a, int k_per_s
     for (int s = 0; s < 2; ++s) {
       u32x4 yf[WM / 16], xf[WN / 16];
 #pragma unroll
-      for (int i = 0; i < WM / 16; ++i) yf[i] = TileLoader<T, BM, AK, NT>::frag(sa, s, wm0 + i * 16);
+      for (int i = 0; i < WM / 16; ++i) yf[i] = TileLoader<BM, AK, NT>::frag(sa, s, wm0 + i * 16);
 #pragma unroll
-      for (int j = 0; j < WN / 16; ++j) xf[j] = TileLoader<T, BN, BK, NT>::frag(sb, s, wn0 + j * 16);
+      for (int j = 0; j < WN / 16; ++j) xf[j] = TileLoader<BN, BK, NT>::frag(sb, s, wn0 + j * 16);
 #pragma unroll
       for (int i = 0; i < WM / 16; ++i)
 #pragma unroll
@@ -349,7 +388,7 @@ __global__ void __launch_bounds__(CF::NT, 1) gemm_kernel(GemmArgs a, int k_per_s
       for (int h = CH / 2; h > 0; h /= 2)
 #pragma unroll
         for (int c = 0; c < h; ++c) acc[c][i][j] += acc[c + h][i][j];
-      epilogue<T, TO, EPI>(a, m0 + wm0 + i * 16 + (l & 15), n0 + wn0 + j * 16 + 4 * (l >> 4), acc[0][i][j]);
+      epilogue<EPI>(a, m0 + wm0 + i * 16 + (l & 15), n0 + wn0 + j * 16 + 4 * (l >> 4), acc[0][i][j]);
     }
 }
 
@@ -363,7 +402,7 @@ __global__ void __launch_bounds__(CF::NT, 1) gemm_kernel(GemmArgs a, int k_per_s
 //             8 lanes fetch one 128-byte row segment, and a 16-row fragment
 //             read touches 16 distinct bank groups;
 //   MN-major  [k][rows] with 16-byte chunk c of line k at c ^ trt_swz(k),
-//             read by ds_read_b64_tr_b16 (see lds_frag_tr).
+//             read by ds_read_b64_tr_b16 (see lds_frag_tr_at).
 // Slots outside the operand (rows past M or N, k past K) are filled from a
 // zero page, so the ring never holds stale data and the k tail sums exactly.
 // The loads of tile kt + NS are issued right after the barrier that publishes
@@ -820,9 +859,8 @@ __global__ void __launch_bounds__(CF::NT, CF::OCC) gemm_pipe_kernel(GemmArgs a, 
   const uint32_t smem_lds = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) u32x4*)smem);
   const int wu = __builtin_amdgcn_readfirstlane(w);
   // Per-thread load addresses at contracted offset 0. When every k-step lies
-  // wholly inside K, a load is one address add (kf: true; a segmented B adds
-  // its segment's offset, one per k-step); fills past the last k-step then
-  // repeat the last one's addresses, into stages that are never read.
+  // wholly inside K, a load is one address add (kf: true); fills past the last
+  // k-step then repeat the last one's addresses, into stages that are never read.
   // Otherwise each load masks itself against K and the operand (pipe_fill_one).
   const bool kfull = k_end - k_begin >= BKE && (k_end - k_begin) % BKE == 0;   // uniform
   const bf16* fa[CF::LA];
@@ -842,30 +880,10 @@ __global__ void __launch_bounds__(CF::NT, CF::OCC) gemm_pipe_kernel(GemmArgs a, 
         dma16(fa[p] + (AK ? (int64_t)kc : (int64_t)kc * a.lda), st + (uint32_t)(blk * 64 * 16));
       } else {
         const int q = p - CF::LA, blk = q * (NT / 64) + wu;
-        int64_t off = BK ? (int64_t)kc : (int64_t)kc * a.ldb;
-        if constexpr (!AK && !BK) {
-          if (a.seg_rows > 0) {   // uniform: row kc of the window is row kc - sg * seg_rows of segment sg
-            const int sg = kc / (int)a.seg_rows;
-            off = (int64_t)((a.seg_first + sg) % a.seg_count) * a.seg_stride +
-                  (int64_t)(kc - sg * (int)a.seg_rows) * a.ldb;
-          }
-        }
-        dma16(fb[q] + off, st + CF::SLOTS_A * 16 + (uint32_t)(blk * 64 * 16));
+        dma16(fb[q] + (BK ? (int64_t)kc : (int64_t)kc * a.ldb), st + CF::SLOTS_A * 16 + (uint32_t)(blk * 64 * 16));
       }
     } else if (p < CF::LA) {
       pipe_fill_one<BM, AK, NT>(p, A, a.lda, m0, a.M, k0, k_end, st, a.zeros, wu, l);
-    } else if constexpr (!AK && !BK) {
-      // weight gradients: B may come in segments of seg_rows contracted rows
-      // (a tile never straddles two); past k_end the rows are masked as usual
-      const bf16* Bs = B;
-      int kb = k0, ke = k_end;
-      if (a.seg_rows > 0) {
-        const int sg = k0 / (int)a.seg_rows;
-        Bs = B + (int64_t)((a.seg_first + sg) % a.seg_count) * a.seg_stride;
-        kb = k0 - sg * (int)a.seg_rows;
-        ke = k_end - sg * (int)a.seg_rows;
-      }
-      pipe_fill_one<BN, BK, NT>(p - CF::LA, Bs, a.ldb, n0, a.N, kb, ke, st + CF::SLOTS_A * 16, a.zeros, wu, l);
     } else {
       pipe_fill_one<BN, BK, NT>(p - CF::LA, B, a.ldb, n0, a.N, k0, k_end, st + CF::SLOTS_A * 16, a.zeros, wu, l);
     }
@@ -1179,43 +1197,32 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_kernel(GemmArgs a, int k_per_s
       for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TJ; ++j) acc[h][g][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  // The bf16 residual or gelu'(u) rows of a one-panel epilogue and the bias, in
-  // registers by the epilogue. They are loaded after the last k-tile's loads
-  // have been issued: vmcnt counts in order, so loaded at the start the first
-  // k-tile would wait for them (measured 1.6 us for the bias and 3.2 us with the
-  // residual rows, of a 25 us product), and in the middle a later one would.
-  constexpr bool PRE = (EPI == EPI_BIAS_RES || EPI == EPI_GELU_GRAD) && sizeof(TO) == 2 && CF::PR == BM;
+  // The bias, in registers by the epilogue. It is loaded after the last k-tile's
+  // loads have been issued: vmcnt counts in order, so loaded at the start the first
+  // k-tile would wait for it (measured 1.6 us of a 25 us product), and in the middle
+  // a later one would. BN = 128 has no epilogue that takes a bias.
   constexpr bool HAS_BIAS = EPI == EPI_BIAS || EPI == EPI_BIAS_RES || EPI == EPI_BIAS_GELU;
+  static_assert(BN == 256 || EPI == EPI_STORE || EPI == EPI_ACC || EPI == EPI_ATOMIC, "no loads but the k-tiles'");
   using EG = EpiGeom<TO, BN, CF::PR, NT>;
-  u32x4 pre[EG::P];
+  u32x4 pre[EG::P];   // (aux rows are loaded panel by panel in the epilogue)
   float pb[EG::U];
   // n_late: the loads in flight behind the k-tiles' when they were all issued
-  // unconditionally (a whole tile, aligned), else 0 (the waits then cover them)
-  constexpr int N_LATE = (PRE ? EG::P : 0) + (HAS_BIAS ? EG::U / 4 : 0);
-  auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  const bool whole = m0 + BM <= a.M && n0 + BN <= a.N && (!PRE || (a.ld_aux % 8 == 0 && al16(a.aux))) &&
-                     (!HAS_BIAS || al16(a.bias));   // uniform
+  // unconditionally (whole columns, aligned), else 0 (the waits then cover them)
+  constexpr int N_LATE = HAS_BIAS ? EG::U / 4 : 0;
+  const bool whole = n0 + BN <= a.N && (reinterpret_cast<uintptr_t>(a.bias) & 15) == 0;   // uniform
   const int n_late = whole ? N_LATE : 0;
   auto late_loads = [&] {
-    if constexpr (N_LATE > 0) {
+    if constexpr (HAS_BIAS) {
       if (whole) {
-        const int n = n0 + (tid % EG::UPR) * EG::U, r0 = tid / EG::UPR;
-        if constexpr (PRE) {
+        const int n = n0 + (tid % EG::UPR) * EG::U;
 #pragma unroll
-          for (int p = 0; p < EG::P; ++p)
-            pre[p] = ld16g(reinterpret_cast<const bf16*>(a.aux) + (int64_t)(m0 + r0 + p * EG::RPI) * a.ld_aux + n);
-        }
-        if constexpr (HAS_BIAS) {
+        for (int q = 0; q < EG::U / 4; ++q) {
+          const u32x4 v = ld16g(a.bias + n + 4 * q);
 #pragma unroll
-          for (int q = 0; q < EG::U / 4; ++q) {
-            const u32x4 v = ld16g(a.bias + n + 4 * q);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) pb[4 * q + j] = vget<float>(v, j);
-          }
+          for (int j = 0; j < 4; ++j) pb[4 * q + j] = vget<float>(v, j);
         }
       } else {
-        if constexpr (PRE) prefetch_aux<TO, BN, CF::PR, NT>(a, m0, n0, tid, pre);
-        if constexpr (HAS_BIAS) prefetch_bias<TO, BN, CF::PR, NT>(a, n0, tid, pb);
+        prefetch_bias<TO, BN, CF::PR, NT>(a, n0, tid, pb);
       }
     }
   };
@@ -1398,7 +1405,7 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_kernel(GemmArgs a, int k_per_s
         load_b(full, kt + 3, ldsb + sb3, IC<0>{}, IC<1>{}, IC<0>{});
         pb_ = cur;
       }
-      wait_but(full, IC<9>{}, kt > nk - 3 ? n_late : 0, nk - kt, 0, 4, 7);
+      wait_but(full, IC<9>{}, 0, nk - kt, 0, 4, 7);
       end_slot();
       matrix_slot(acc[0][0], x);
 
@@ -1410,8 +1417,7 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_kernel(GemmArgs a, int k_per_s
       pb3 = pb_;
       next_a();
       next_b();
-      if (!decltype(full)::value && kt == nk - 3) late_loads();
-      wait_but(full, IC<9>{}, kt >= nk - 3 ? n_late : 0, nk - kt, 0, 2, 6, 8);
+      wait_but(full, IC<9>{}, 0, nk - kt, 0, 2, 6, 8);
       end_slot();
       matrix_slot(acc[1][0], x);
       sa = sa == 2 * AST ? 0 : sa + AST;
@@ -1440,8 +1446,7 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_kernel(GemmArgs a, int k_per_s
     load_b(TAIL, 3, ldsb, IC<0>{}, IC<0>{}, IC<3 * SUBB>{});
     pb3 = pb_;
     next_b();
-    if (nk < 3) late_loads();
-    wait_but(TAIL, IC<9>{}, nk < 3 ? n_late : 0, nk + 1, 0, 2, 6, 8);   // B of tiles 0 and 1, A_0 of tile 0
+    wait_but(TAIL, IC<9>{}, 0, nk + 1, 0, 2, 6, 8);   // B of tiles 0 and 1, A_0 of tile 0
     end_slot();
     read_b(slot_b(0, 0), fb0, 0, TJ);
     if (group == 1) end_slot();
@@ -1474,11 +1479,11 @@ __global__ void __launch_bounds__(512, 2) gemm_pp_kernel(GemmArgs a, int k_per_s
                 acc[h][g][i][j];
     }
   };
-  staged_epilogue<TO, EPI, CF, PRE>(a, cl, m0, n0, put, pre, pb);
+  staged_epilogue<TO, EPI, CF, false>(a, cl, m0, n0, put, pre, pb);
 }
 
 
-// Tile configurations; the choice per call is made in launch().
+// Tile configurations.
 typedef Tile<128, 128, 64, 64> T128x128;
 typedef Tile<64, 64, 32, 32, 4> T64x64;
 typedef Tile<32, 32, 16, 16, 4> T32x32;
@@ -1513,15 +1518,31 @@ hipError_t launch_pp(const GemmArgs& a, int splits, hipStream_t st) {
 }
 
 
-template <typename T, typename TO, bool AK, bool BK, int EPI, class CF>
+template <bool AK, bool BK, int EPI, class CF>
 hipError_t launch_cf(const GemmArgs& a, int splits, hipStream_t st) {
-  constexpr int BKE = KVN * Vec<T>::V;
+  constexpr int BKE = KVN * Vec<float>::V;
   const int tiles = ((a.M + CF::BM - 1) / CF::BM) * ((a.N + CF::BN - 1) / CF::BN);
   int kps = (a.K + splits - 1) / splits;
   kps = ((kps + BKE - 1) / BKE) * BKE;
   const int used = (a.K + kps - 1) / kps;
-  hipLaunchKernelGGL((gemm_kernel<T, TO, AK, BK, EPI, CF>), dim3(tiles, used), dim3(CF::NT), 0, st, a, kps);
+  hipLaunchKernelGGL((gemm_kernel<AK, BK, EPI, CF>), dim3(tiles, used), dim3(CF::NT), 0, st, a, kps);
   return hipGetLastError();
+}
+
+template <bool AK, bool BK, int EPI>
+hipError_t launch_f32(const GemmArgs& a, int splits, hipStream_t st) {
+  if (a.seg_rows > 0) return hipErrorInvalidValue;
+  hipError_t e;
+  switch (gemm_f32_tile(AK ? (BK ? GEMM_NT : GEMM_NN) : GEMM_TN, a.M, a.N, a.K, splits)) {
+    case 32: e = launch_cf<AK, BK, EPI, T32x32>(a, splits, st); break;
+    case 64: e = launch_cf<AK, BK, EPI, T64x64>(a, splits, st); break;
+    default: e = launch_cf<AK, BK, EPI, T128x128>(a, splits, st); break;
+  }
+  if constexpr (EPI != EPI_ATOMIC && EPI != EPI_ACC) {
+    // the register-staged epilogue has no column sums: one pass over the output
+    if (e == hipSuccess && a.colsum != nullptr) e = colsum_acc(DT_F32, a.C, a.ldc, a.M, a.N, a.colsum, st);
+  }
+  return e;
 }
 
 // The pipelined kernels move whole 16-byte chunks of 8 elements from global
@@ -1531,8 +1552,8 @@ hipError_t launch_cf(const GemmArgs& a, int splits, hipStream_t st) {
 // zero-padded and B MN-major; both MN-major: any K. A chunk of an MN-major
 // operand that straddles M or N only feeds outputs that are not stored, and
 // must exist: M (N) a multiple of 8, or a leading dimension that covers the
-// chunk. Other calls take the register-staged kernel, which masks partial
-// vectors.
+// chunk. Other calls are refused: every bf16 operand of a stage is aligned (d and
+// f are multiples of 32).
 template <bool AK, bool BK>
 bool pipe_eligible(const GemmArgs& a) {
   auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
@@ -1551,187 +1572,126 @@ bool pp_reach(const GemmArgs& a) {
   return a.lda < (AK ? 1 << 23 : 1 << 26) && a.ldb < (BK ? 1 << 23 : 1 << 26);
 }
 
-// Tiles and split-K count of a window weight gradient: long contractions over
-// few output tiles, so K is split until one round of workgroups (the CUs) is
-// full, each split at least 512 rows, and of the two tile widths the one with
-// the least work per CU is taken, a 256 x 256 tile costing 1.8 of 256 x 128.
-// Atomic adds grow with the splits, at most 32. At 768-wide blocks over 32768
-// rows: 3072 x 768 in 207 us with the three-stage ring on 256 x 128 tiles (two
-// rounds), 196 ping-pong, 172 on 252 of 256 x 256; 2304 x 768 170, 160, 138; 768
-// x 768 114, 112, 93. About 60 us of each are the atomic adds, which cross the
-// XCDs in memory.
-struct WindowPlan { int bn, splits; };
-WindowPlan window_plan(int M, int N, int64_t K) {
-  WindowPlan best{128, 1};
-  double best_t = 1e30;
-  const int cus = cu_count();
-  for (int bn : {256, 128}) {
-    const int64_t tiles = (int64_t)((M + 255) / 256) * ((N + bn - 1) / bn), kt = (K + 63) / 64;
-    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(32, K / 512));
-    const int sp = (int)std::max<int64_t>(1, std::min(most, cus / tiles));
-    const double t = (double)((tiles * sp + cus - 1) / cus) * (double)((kt + sp - 1) / sp) * (bn == 256 ? 1.8 : 1.0);
-    if (t < best_t) {
-      best_t = t;
-      best = {bn, sp};
-    }
-  }
-  return best;
-}
-
-template <typename T, typename TO, bool AK, bool BK, int EPI>
-hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
-  if (a.seg_rows > 0) {
-    // segmented B (the window weight gradients): ping-pong tiles, see gemm_window_splits
-    if constexpr (sizeof(T) == 2 && !AK && !BK) {
-      if (pipe_eligible<AK, BK>(a) && pp_reach<AK, BK>(a) && a.seg_rows % 64 == 0 && a.seg_count >= 1 && a.seg_first >= 0)
-        return window_plan(a.M, a.N, a.K).bn == 256 ? launch_pp<TO, AK, BK, EPI, 256>(a, splits, st)
-                                                    : launch_pp<TO, AK, BK, EPI, 128>(a, splits, st);
-    }
+// A segmented B: the window weight gradients.
+template <int EPI>
+hipError_t launch_window(const GemmArgs& a, int splits, hipStream_t st) {
+  if (!pipe_eligible<false, false>(a) || !pp_reach<false, false>(a) || a.seg_rows % 64 || a.seg_count < 1 ||
+      a.seg_first < 0)
     return hipErrorInvalidValue;
+  return gemm_window_plan(a.M, a.N, a.K).bn == 256 ? launch_pp<float, false, false, EPI, 256>(a, splits, st)
+                                                   : launch_pp<float, false, false, EPI, 128>(a, splits, st);
+}
+
+// Both operands K-major (a block's forward products and, on the transposed
+// weights, its input gradients), on the tiles of gemm_kmajor_plan.
+template <int EPI>
+hipError_t launch_kmajor(const GemmArgs& a, hipStream_t st) {
+  KmajorPlan plan = gemm_kmajor_plan(a.M, a.N);
+  if (!pp_reach<true, true>(a) && (plan.tile == KT_PP_256x256 || plan.n1 > 0)) plan = {KT_256x128, 0};
+  if (plan.n1 > 0) {
+    GemmArgs r = a;
+    r.N = plan.n1;
+    const hipError_t e = launch_kmajor<EPI>(r, st);
+    if (e != hipSuccess) return e;
+    auto skip = [&](auto* p) { return p == nullptr ? p : p + plan.n1; };
+    r.N = a.N - plan.n1;
+    r.B = reinterpret_cast<const bf16*>(a.B) + plan.n1 * a.ldb;
+    r.C = reinterpret_cast<bf16*>(a.C) + plan.n1;
+    r.C2 = skip(reinterpret_cast<bf16*>(a.C2));
+    r.bias = skip(a.bias);
+    r.aux = skip(reinterpret_cast<const bf16*>(a.aux));
+    r.colsum = skip(a.colsum);
+    return launch_kmajor<EPI>(r, st);
   }
-  if constexpr (sizeof(T) == 2) {
-    if (pipe_eligible<AK, BK>(a)) {
-      // Grids that leave CUs idle: the largest tiles that still fit one round. A
-      // k-tile takes about 0.2 us on 64 x 64 tiles, 0.24 on 128 x 64, 0.36 on
-      // 128 x 128 and 0.6-0.8 on 256 x 128, so below one round of tiles the
-      // smaller ones win (128 x 768 x 3072: 34.1 us on 256 x 128, 12.8 on 64 x
-      // 64; 2048 x 768 x 3072: 36.9, 21.9 on 384 of 64 x 64, 18.3 on 192 of 128
-      // x 64; 4096 x 1024 x 4096: 48.8, 54.4, 49.1, 38.5 on 256 of 128 x 128),
-      // above it the larger ones, which re-read the operands less.
-      if constexpr (AK && BK && sizeof(TO) == 2) {
-        const int64_t cus = cu_count();
-        auto tiles = [&](int bm, int bn) { return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-        if (splits == 1) {
-          if (tiles(64, 64) <= cus) return launch_pipe<TO, AK, BK, EPI, P64x64>(a, splits, st);
-          if (tiles(128, 64) <= cus) return launch_pipe<TO, AK, BK, EPI, P128x64>(a, splits, st);
-          if (tiles(128, 128) <= cus) return launch_pipe<TO, AK, BK, EPI, P128x128w8>(a, splits, st);
-        }
-      }
-      // 256 x 256 ping-pong tiles where they take fewer rounds of the CUs than
-      // 256 x 128 ring tiles, a round of them costing 1.8 of the others (whole
-      // rounds at 8192 x 4096 x 1024, in the stage: FFN1 forward 106 -> 88.9 us,
-      // FFN2 input gradient 110 -> 82.2; at 8192 x 2048, mean of K 2048 and
-      // 8192: residual 163 -> 131, plain 157 -> 131; qkv 8192 x 6144 x 2048:
-      // 209 -> 170).
-      // Otherwise weight gradients (both operands MN-major) and the input
-      // gradient through gelu'(u): 128 x 128 tiles, two workgroups per CU, so
-      // one's epilogue overlaps the other's loop (3-6% faster for the latter,
-      // slower for the other forward and input-gradient products: qkv 67 -> 69
-      // us); the rest: 256 x 128 tiles, which re-read the weights half as often.
-      if constexpr (AK && BK && sizeof(TO) == 2) {
-        const int64_t tm = (a.M + 255) / 256, cus = cu_count();
-        auto rounds = [&](int64_t n, int bn) { return (double)((tm * ((n + bn - 1) / bn) + cus - 1) / cus); };
-        if (splits == 1 && pp_reach<AK, BK>(a)) {
-          const double wide = 1.8 * rounds(a.N, 256), narrow = rounds(a.N, 128);
-          // Columns of whole 256 x 256 rounds, the others in a launch of their own:
-          // 8192 x 3072 as 2048 + 1024, at K 1024 qkv 67 -> 36.9 + 23.4 us; at K
-          // 768 FFN1 forward 68.6 -> 39.3 + 24.4, FFN2 input gradient 65 -> 36.4 +
-          // 25.0; qkv 8192 x 2304 x 768 (2048 + 256) 54.5 -> 29.9 + 9.5.
-          const int64_t per = cus % tm == 0 ? cus / tm * 256 : 0, n1 = per > 0 ? a.N / per * per : 0;
-          if (n1 > 0 && n1 < a.N && 1.8 * rounds(n1, 256) + rounds(a.N - n1, 128) + 0.1 < std::min(wide, narrow)) {
-            GemmArgs r = a;
-            r.N = (int)n1;
-            const hipError_t e = launch<T, TO, AK, BK, EPI>(r, 1, st);
-            if (e != hipSuccess) return e;
-            auto skip = [&](auto* p) { return p == nullptr ? p : p + n1; };
-            r.N = a.N - (int)n1;
-            r.B = reinterpret_cast<const T*>(a.B) + n1 * a.ldb;
-            r.C = reinterpret_cast<TO*>(a.C) + n1;
-            r.C2 = skip(reinterpret_cast<TO*>(a.C2));
-            r.bias = skip(a.bias);
-            r.aux = skip(reinterpret_cast<const T*>(a.aux));
-            r.colsum = skip(a.colsum);
-            return launch<T, TO, AK, BK, EPI>(r, 1, st);
-          }
-          if (wide < narrow) return launch_pp<TO, AK, BK, EPI, 256>(a, splits, st);
-        }
-      }
-      // An MN-major weight operand (the LM head's input gradient, K = V):
-      // 256 x 128 ping-pong tiles, whose partial last k-tile does not slow
-      // the others (8192 x 1024 x 50257: 1115 us on the register-staged
-      // kernel, 690 now).
-      if constexpr (AK && !BK && EPI == EPI_STORE) {
-        if (pp_reach<AK, BK>(a)) return launch_pp<TO, AK, BK, EPI, 128>(a, splits, st);
-      }
-      if constexpr (!AK || EPI == EPI_GELU_GRAD) return launch_pipe<TO, AK, BK, EPI, P128x128o2>(a, splits, st);
-      else return launch_pipe<TO, AK, BK, EPI, P256x128>(a, splits, st);
-    }
+  switch (plan.tile) {
+    case KT_64x64: return launch_pipe<bf16, true, true, EPI, P64x64>(a, 1, st);
+    case KT_128x64: return launch_pipe<bf16, true, true, EPI, P128x64>(a, 1, st);
+    case KT_128x128: return launch_pipe<bf16, true, true, EPI, P128x128w8>(a, 1, st);
+    case KT_PP_256x256: return launch_pp<bf16, true, true, EPI, 256>(a, 1, st);
+    default: break;
   }
-  hipError_t e;
-  if constexpr (sizeof(T) == 4) {
-    switch (gemm_f32_tile(AK ? (BK ? GEMM_NT : GEMM_NN) : GEMM_TN, a.M, a.N, a.K, splits)) {
-      case 32: e = launch_cf<T, TO, AK, BK, EPI, T32x32>(a, splits, st); break;
-      case 64: e = launch_cf<T, TO, AK, BK, EPI, T64x64>(a, splits, st); break;
-      default: e = launch_cf<T, TO, AK, BK, EPI, T128x128>(a, splits, st); break;
+  // The input gradient through gelu'(u): 128 x 128 tiles, two workgroups per CU, so
+  // one's epilogue overlaps the other's loop (3-6% faster, and slower for the other
+  // products: qkv 67 -> 69 us).
+  if constexpr (EPI == EPI_GELU_GRAD) return launch_pipe<bf16, true, true, EPI, P128x128o2>(a, 1, st);
+  else return launch_pipe<bf16, true, true, EPI, P256x128>(a, 1, st);
+}
+
+template <bool AK, bool BK, int EPI>
+hipError_t launch_bf16(const GemmArgs& a, int splits, hipStream_t st) {
+  if (!pipe_eligible<AK, BK>(a)) return hipErrorInvalidValue;
+  if constexpr (AK && BK) {
+    return launch_kmajor<EPI>(a, st);
+  } else if constexpr (AK) {
+    // An MN-major weight operand (the LM head's input gradient, K = V): 256 x 128
+    // ping-pong tiles, whose partial last k-tile does not slow the others (8192 x
+    // 1024 x 50257: 1118 us on the register-staged kernel, 683 now).
+    if constexpr (EPI == EPI_STORE) {
+      if (pp_reach<AK, BK>(a)) return launch_pp<bf16, AK, BK, EPI, 128>(a, splits, st);
     }
+    if constexpr (EPI == EPI_GELU_GRAD) return launch_pipe<bf16, AK, BK, EPI, P128x128o2>(a, splits, st);
+    else return launch_pipe<bf16, AK, BK, EPI, P256x128>(a, splits, st);
   } else {
-    return hipErrorInvalidValue;   // every bf16 operand of a stage is aligned (d and f multiples of 32)
-  }
-  if constexpr (EPI != EPI_ATOMIC && EPI != EPI_ACC) {
-    // the register-staged epilogue has no column sums: one pass over the output
-    if (e == hipSuccess && a.colsum != nullptr)
-      e = colsum_acc(sizeof(TO) == 2 ? DT_BF16 : DT_F32, a.C, a.ldc, a.M, a.N, a.colsum, st);
-  }
-  return e;
-}
-
-template <typename T, typename TO, bool AK, bool BK>
-hipError_t by_epi(GemmEpi epi, const GemmArgs& a, int splits, hipStream_t st) {
-  switch (epi) {
-    case EPI_STORE: return launch<T, TO, AK, BK, EPI_STORE>(a, splits, st);
-    case EPI_BIAS: return launch<T, TO, AK, BK, EPI_BIAS>(a, splits, st);
-    case EPI_BIAS_RES: return launch<T, TO, AK, BK, EPI_BIAS_RES>(a, splits, st);
-    case EPI_BIAS_GELU: return launch<T, TO, AK, BK, EPI_BIAS_GELU>(a, splits, st);
-    case EPI_GELU_GRAD: return launch<T, TO, AK, BK, EPI_GELU_GRAD>(a, splits, st);
-    default: return hipErrorInvalidValue;
+    // weight gradients: 128 x 128 tiles, two workgroups per CU
+    return launch_pipe<float, AK, BK, EPI, P128x128o2>(a, splits, st);
   }
 }
 
-template <typename T, bool AK, bool BK>
-hipError_t by_epi_acc(GemmEpi epi, const GemmArgs& a, int splits, hipStream_t st) {
-  if (epi == EPI_ACC) return launch<T, float, AK, BK, EPI_ACC>(a, 1, st);
-  if (epi == EPI_ATOMIC) return launch<T, float, AK, BK, EPI_ATOMIC>(a, splits, st);
-  return hipErrorInvalidValue;
+template <DType DT, bool AK, bool BK, int EPI>
+hipError_t launch(const GemmArgs& a, int splits, hipStream_t st) {
+  if constexpr (DT == DT_F32) {
+    return launch_f32<AK, BK, EPI>(a, splits, st);
+  } else {
+    if constexpr (!AK && !BK) {
+      if (a.seg_rows > 0) return launch_window<EPI>(a, splits, st);
+    }
+    return a.seg_rows > 0 ? hipErrorInvalidValue : launch_bf16<AK, BK, EPI>(a, splits, st);
+  }
 }
 
-template <typename T>
+// The softmax cross-entropy products.
+hipError_t launch_ce(bool out_f32, GemmEpi epi, const GemmArgs& a, hipStream_t st) {
+  if (!pipe_eligible<true, true>(a) || !pp_reach<true, true>(a) || a.row_tgt == nullptr || a.colsum != nullptr)
+    return hipErrorInvalidValue;
+  // 256 x 256 ping-pong tiles (8192 x 50257 x 1024: 1111 us storing fp32 logits on 256 x 128
+  // ring tiles, 1115 with the statistics, which save a 950 us pass over the logits; without
+  // logits 1079 -> 871 and 1203 -> 978 us). About 100 us of each are the exponentials: with a
+  // once-rounded argument 2^(x log2 e) they took 1015, 736 and 872 us, but were off by up to
+  // |x| 2^-24 where expf is good to an ulp.
+  if (epi == EPI_CE_GRAD) {
+    if (a.row_lse == nullptr || out_f32) return hipErrorInvalidValue;
+    return launch_pp<bf16, true, true, EPI_CE_GRAD, 256>(a, 1, st);
+  }
+  if (a.ce_part == nullptr || a.ce_zt == nullptr || a.ld_part < (a.N + 63) / 64) return hipErrorInvalidValue;
+  if (epi == EPI_STORE_CE) return launch_pp<float, true, true, EPI_STORE_CE, 256>(a, 1, st);
+  return launch_pp<float, true, true, EPI_CE_STATS, 256>(a, 1, st);
+}
+
+template <DType DT>
 hipError_t by_layout(bool out_f32, GemmLayout lay, GemmEpi epi, const GemmArgs& a, int splits, hipStream_t st) {
   if (epi == EPI_ACC || epi == EPI_ATOMIC) {
     // accumulation into fp32 is only used for weight gradients
-    if (lay == GEMM_TN) return by_epi_acc<T, false, false>(epi, a, splits, st);
-    return hipErrorInvalidValue;
+    if (lay != GEMM_TN) return hipErrorInvalidValue;
+    return epi == EPI_ACC ? launch<DT, false, false, EPI_ACC>(a, 1, st)
+                          : launch<DT, false, false, EPI_ATOMIC>(a, splits, st);
   }
   if (splits != 1) return hipErrorInvalidValue;
-  if (epi == EPI_CE_STATS || epi == EPI_STORE_CE || epi == EPI_CE_GRAD) {
-    // pipelined bf16 kernel only; the statistics need 64-column groups
-    if constexpr (sizeof(T) == 2) {
-      if (lay != GEMM_NT || !pipe_eligible<true, true>(a) || a.row_tgt == nullptr || a.colsum != nullptr)
-        return hipErrorInvalidValue;
-      // 256 x 256 ping-pong tiles (8192 x 50257 x 1024: 1111 us storing fp32 logits on 256 x 128
-      // ring tiles, 1115 with the statistics, which save a 950 us pass over the logits; without
-      // logits 1079 -> 871 and 1203 -> 978 us). About 100 us of each are the exponentials: with a
-      // once-rounded argument 2^(x log2 e) they took 1015, 736 and 872 us, but were off by up to
-      // |x| 2^-24 where expf is good to an ulp.
-      if (epi != EPI_CE_GRAD) {
-        if (a.ce_part == nullptr || a.ce_zt == nullptr || a.ld_part < (a.N + 63) / 64) return hipErrorInvalidValue;
-        if (epi == EPI_STORE_CE) return launch_pp<float, true, true, EPI_STORE_CE, 256>(a, 1, st);
-        return launch_pp<float, true, true, EPI_CE_STATS, 256>(a, 1, st);
-      }
-      if (a.row_lse == nullptr || out_f32) return hipErrorInvalidValue;
-      return launch_pp<T, true, true, EPI_CE_GRAD, 256>(a, 1, st);
-    }
-    return hipErrorInvalidValue;
-  }
+  if (epi == EPI_CE_STATS || epi == EPI_STORE_CE || epi == EPI_CE_GRAD)
+    return DT == DT_BF16 && lay == GEMM_NT ? launch_ce(out_f32, epi, a, st) : hipErrorInvalidValue;
+  if (out_f32 && (DT == DT_BF16 || lay != GEMM_NT || epi != EPI_STORE)) return hipErrorInvalidValue;
   if (lay == GEMM_NT) {
-    if (out_f32) {
-      if (epi != EPI_STORE) return hipErrorInvalidValue;
-      return launch<T, float, true, true, EPI_STORE>(a, 1, st);
+    switch (epi) {
+      case EPI_STORE: return launch<DT, true, true, EPI_STORE>(a, 1, st);
+      case EPI_BIAS: return launch<DT, true, true, EPI_BIAS>(a, 1, st);
+      case EPI_BIAS_RES: return launch<DT, true, true, EPI_BIAS_RES>(a, 1, st);
+      case EPI_BIAS_GELU: return launch<DT, true, true, EPI_BIAS_GELU>(a, 1, st);
+      case EPI_GELU_GRAD: return launch<DT, true, true, EPI_GELU_GRAD>(a, 1, st);
+      default: return hipErrorInvalidValue;
     }
-    return by_epi<T, T, true, true>(epi, a, 1, st);
   }
-  if (lay == GEMM_NN && !out_f32) {
-    if (epi == EPI_STORE) return launch<T, T, true, false, EPI_STORE>(a, 1, st);
-    if (epi == EPI_GELU_GRAD) return launch<T, T, true, false, EPI_GELU_GRAD>(a, 1, st);
+  if (lay == GEMM_NN) {
+    if (epi == EPI_STORE) return launch<DT, true, false, EPI_STORE>(a, 1, st);
+    if (epi == EPI_GELU_GRAD) return launch<DT, true, false, EPI_GELU_GRAD>(a, 1, st);
   }
   return hipErrorInvalidValue;
 }
@@ -1865,7 +1825,7 @@ int gemm_acc_splits(DType dt, int M, int N, int K) {
       return sp > kt ? 1e30 : std::ceil(tiles * sp / (cu_count() * OCC)) * std::ceil((double)kt / sp) * t_k;
     });
   }
-  // fp32: k-tiles of 32 on the tile edge launch() takes for that many splits
+  // fp32: k-tiles of 32 on the tile edge for that many splits
   const int kt = (K + 31) / 32;
   return best_of([&](int sp) {
     if (sp > kt) return 1e30;
@@ -1874,8 +1834,6 @@ int gemm_acc_splits(DType dt, int M, int N, int K) {
     return std::ceil(tiles * sp / (2 * cu_count())) * std::ceil((double)kt / sp) * t_k;
   });
 }
-
-int gemm_window_splits(int M, int N, int64_t K) { return window_plan(M, N, K).splits; }
 
 hipError_t gemm_wgrad(DType dt, const GemmArgs& a, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0 || a.K <= 0 || a.colsum != nullptr || a.seg_rows > 0) return hipErrorInvalidValue;
@@ -1905,8 +1863,8 @@ hipError_t gemm(DType dt, bool out_f32, GemmLayout lay, GemmEpi epi, const GemmA
                 hipStream_t st) {
   if (a.M <= 0 || a.N <= 0 || a.K <= 0 || splits < 1) return hipErrorInvalidValue;
   if (a.colsum != nullptr && (epi == EPI_ACC || epi == EPI_ATOMIC)) return hipErrorInvalidValue;
-  if (dt == DT_BF16) return by_layout<bf16>(out_f32, lay, epi, a, splits, st);
-  return by_layout<float>(out_f32, lay, epi, a, splits, st);
+  if (dt == DT_BF16) return by_layout<DT_BF16>(out_f32, lay, epi, a, splits, st);
+  return by_layout<DT_F32>(out_f32, lay, epi, a, splits, st);
 }
 
 }  // namespace paci

@@ -121,8 +121,15 @@ hipError_t gemm_wgrad(DType dt, const GemmArgs& a, hipStream_t st);
 hipError_t gemm(DType dt, bool out_f32, GemmLayout lay, GemmEpi epi, const GemmArgs& a, int splits, hipStream_t st);
 // Tile edge (128, 64 or 32) of an fp32 product.
 int gemm_f32_tile(GemmLayout lay, int M, int N, int K, int splits);
-// Split-K count of a window weight gradient (GEMM_TN, segmented B) over K rows.
-int gemm_window_splits(int M, int N, int64_t K);
+// Tiles of a bf16 product with both operands K-major. n1 > 0: columns [0, n1) and
+// the others are two launches, each on a plan of its own.
+enum KmajorTile { KT_256x128 = 0, KT_PP_256x256, KT_128x128, KT_128x64, KT_64x64 };
+struct KmajorPlan { KmajorTile tile; int n1; };
+KmajorPlan gemm_kmajor_plan(int M, int N);
+// Tile columns (256 or 128; 256 rows) and split-K count of a window weight
+// gradient (GEMM_TN, segmented B) over K rows.
+struct WindowPlan { int bn, splits; };
+WindowPlan gemm_window_plan(int M, int N, int64_t K);
 
 // ---- causal attention over the fused projection qkv [T, 3d] --------------------------
 // Forward: o [T, d]; lse2 [mu*H*S] = log2-sum-exp2 of the scaled scores in log2 units.

@@ -877,7 +877,7 @@ int window_wgrad(paci_stage* h, size_t dy_off, size_t x_off, int out, int in, in
                  int64_t g_off) {
   const Layout& L = h->L;
   const int64_t Kt = (int64_t)n * L.T;
-  const int splits = paci::gemm_window_splits(out, in, Kt);
+  const int splits = paci::gemm_window_plan(out, in, Kt).splits;
   paci::GemmArgs a{h->win(dy_off, j0, out), out, h->arena + L.stash + x_off, in, out, in, (int)Kt, h->g(g_off), in,
                    nullptr, nullptr, 0, nullptr, h->arena + L.zeros};
   a.seg_rows = L.T;
