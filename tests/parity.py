@@ -102,16 +102,21 @@ def small_cfg(name, **kw):
         "win_bf16": dict(kind="middle", n_layers=2, d_model=128, n_heads=2, head_dim=64, d_ff=384, seq=64,
                          micro_batch=2, K=3, delay=2, M=9, dtype="bf16", window=1),
         # 8 micro-batches of T = 1024 per window: the window GEMMs split the 8192
-        # contracted rows 8 ways, each split one activation segment
+        # contracted rows 16 ways, two splits to an activation segment
         "win8_bf16": dict(kind="middle", n_layers=1, d_model=128, n_heads=2, head_dim=64, d_ff=256, seq=512,
                           micro_batch=2, K=8, delay=2, M=16, dtype="bf16", window=1),
-        # T = 320, K = 7: the 2240 contracted rows of a window split in two at row
-        # 1152, inside the fourth activation segment (rows 960 .. 1279), as the
+        # T = 320, K = 7: the 2240 contracted rows of a window split in four at rows
+        # 576, 1152 and 1728, each inside an activation segment (of 320 rows), as the
         # full-size window products split mid-segment
         "winsplit_bf16": dict(kind="middle", n_layers=1, d_model=128, n_heads=2, head_dim=64, d_ff=256, seq=160,
                               micro_batch=2, K=7, delay=2, M=14, dtype="bf16", window=1),
+        # d 1504, T = 128, K = 9: the QKV window product runs on 256 x 256 tiles (ragged
+        # on both sides), its 1152 rows split in two at row 576, inside a segment; a
+        # segment is two k-tiles, and the second window's segments wrap around the slots
+        "winwide_bf16": dict(kind="middle", n_layers=1, d_model=1504, n_heads=47, head_dim=32, d_ff=96, seq=64,
+                             micro_batch=2, K=9, delay=2, M=18, dtype="bf16", window=1),
         # FFN width 2304 at T = 4096: the FFN1 forward and FFN2 input-gradient products
-        # have 288 tiles of 256 x 128, more than the 256 CUs (a second, partial round)
+        # run on 144 tiles of 256 x 256 (a partial round, where 256 x 128 tiles take two)
         "wide_bf16": dict(kind="middle", n_layers=1, d_model=256, n_heads=4, head_dim=64, d_ff=2304, seq=512,
                           micro_batch=8, K=2, delay=1, M=6, dtype="bf16"),
         # T = 4000, FFN width 4064, d 96: the FFN1 forward and FFN2 input-gradient
@@ -121,9 +126,12 @@ def small_cfg(name, **kw):
         "tall_bf16": dict(kind="middle", n_layers=1, d_model=96, n_heads=3, head_dim=32, d_ff=4064, seq=500,
                           micro_batch=8, K=2, delay=1, M=3, dtype="bf16"),
         # d 512, FFN 2048: every weight's tile grid of the grouped weight-gradient launch
-        # splits into 8 equal blocks, one per XCD (W_qkv 6 x 4 and W_o 2 x 4 tiles of 256 x 128)
+        # splits into 8 equal blocks, one per XCD (W_qkv 12 x 4 and W_o 4 x 4 tiles of 128 x 128;
+        # with a second block 6 x 4 and 2 x 4 tiles of 256 x 128)
         "xcd_bf16": dict(kind="middle", n_layers=1, d_model=512, n_heads=8, head_dim=64, d_ff=2048, seq=128,
                          micro_batch=2, K=2, delay=1, M=4, dtype="bf16"),
+        "xcd2_bf16": dict(kind="middle", n_layers=2, d_model=512, n_heads=8, head_dim=64, d_ff=2048, seq=128,
+                          micro_batch=2, K=2, delay=1, M=4, dtype="bf16"),
         # the same shapes as win8_bf16 on the default stage (per-backward accumulation)
         "acc8_bf16": dict(kind="middle", n_layers=1, d_model=128, n_heads=2, head_dim=64, d_ff=256, seq=512,
                           micro_batch=2, K=8, delay=2, M=16, dtype="bf16"),

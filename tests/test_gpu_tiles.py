@@ -4,7 +4,7 @@ tolerances are those of the parity tests: bf16 rounding of stored activations)."
 import numpy as np
 import pytest
 
-from parity import rel_err, small_cfg, tol
+from parity import Inputs, compare_replays, forced_oracle, gpu_replay, rel_err, small_cfg, tol
 from test_gpu_stage import _one_event_pair, binding  # noqa: F401  (binding: the fixture)
 
 pytestmark = pytest.mark.gpu
@@ -34,6 +34,14 @@ def test_pingpong_all_products(binding, d):  # noqa: F811
     _check(binding, small_cfg("dh32_bf16", d_model=d, n_heads=d // 32, d_ff=64, seq=83, micro_batch=200))
 
 
+# 256 x 128 ring tiles in more than one round, the last one partial and ragged (T 25500: 100 row
+# tiles; N 1920 six rounds and N 640 two of them): bias, residual and plain products over 1, 10 and
+# 30 k-tiles, then the GELU product and the gelu' one (128 x 128 tiles, two per CU)
+@pytest.mark.parametrize("d,f", [(640, 64), (32, 640)])
+def test_ring_rounds(binding, d, f):  # noqa: F811
+    _check(binding, small_cfg("dh32_bf16", d_model=d, n_heads=d // 32, d_ff=f, seq=85, micro_batch=300))
+
+
 # products split by columns (T 16200: 64 row tiles; N 1440 as 1024 in one round of
 # 256 x 256 tiles and 416 apart): bias, GELU, and gelu' with its column sums
 def test_column_split(binding):  # noqa: F811
@@ -47,10 +55,12 @@ def test_pingpong_grouped(binding, seq, mu):  # noqa: F811
     _check(binding, small_cfg("tall_bf16", d_model=1024, n_heads=16, head_dim=64, d_ff=4096, seq=seq, micro_batch=mu))
 
 
-# grouped weight gradients on the ring kernel's tiles over an odd T
+# grouped weight gradients on the ring kernel's tiles over an odd T: 64 x 64, then 256 x 128 (d 544:
+# ragged, W_1 and W_2 in XCD blocks)
 @pytest.mark.parametrize("seq,mu", [(33, 1), (33, 3), (101, 5)])
 def test_grouped_odd_tokens(binding, seq, mu):  # noqa: F811
     _check(binding, small_cfg("ragged_bf16", seq=seq, micro_batch=mu))
+    _check(binding, small_cfg("dh32_bf16", d_model=544, n_heads=17, d_ff=2048, seq=seq, micro_batch=mu))
 
 
 # LM head on the pipelined kernels at vocabularies that are not multiples of 8:
@@ -65,11 +75,23 @@ def test_lm_head(binding, V, d, seq, mu, fused):  # noqa: F811
                               micro_batch=mu, fused_head=fused))
 
 
-# ping-pong tiles over segments (window products): 1 to 6 k-tiles, one micro-batch,
-# 256 x 256 tiles, 256 x 128 (d 96 and 288), split over K (T 1088)
-@pytest.mark.parametrize("d,T", [(288, 64), (288, 128), (288, 320), (96, 384), (512, 384), (512, 1088)])
+# ping-pong tiles over segments (window products), one micro-batch: 256 x 128 tiles over 1 to 6
+# k-tiles and split over K (T 1088); 256 x 256 tiles, ragged on both sides, for the QKV product over
+# 1 to 3 k-tiles (d 2016) and split over K (d 1504)
+@pytest.mark.parametrize("d,T", [(288, 64), (288, 128), (288, 320), (96, 384), (512, 384), (512, 1088), (2016, 64),
+                                 (2016, 128), (2016, 192), (1504, 1152)])
 def test_pingpong_window(binding, d, T):  # noqa: F811
-    _check(binding, small_cfg("win_bf16", d_model=d, n_heads=d // 32, head_dim=32, d_ff=416, seq=T // 2, micro_batch=2))
+    _check(binding, small_cfg("win_bf16", n_layers=1 if d > 512 else 2, d_model=d, n_heads=d // 32, head_dim=32,
+                              d_ff=96 if d > 512 else 416, seq=T // 2, micro_batch=2))
+
+
+# the same over many segments of one k-tile each: 18 micro-batches of 64 tokens in a window, split
+# over K at a segment's first row
+def test_pingpong_window_short_segments(binding):  # noqa: F811
+    c = small_cfg("winwide_bf16", seq=32, K=18, M=18)
+    inp = Inputs(c, 1, c["M"])
+    g = gpu_replay(c, inp)
+    compare_replays(c, g, forced_oracle(c, inp, g), theta0=inp.params)
 
 
 # bf16 products on the tiles of small grids, ragged on every side: 64 x 64 up to
@@ -78,6 +100,12 @@ def test_pingpong_window(binding, d, T):  # noqa: F811
                                         (960, 64, 100, 11), (320, 992, 200, 11), (960, 96, 200, 11)])
 def test_small_grids_bf16(binding, d, f, seq, mu):  # noqa: F811
     _check(binding, small_cfg("dh32_bf16", d_model=d, n_heads=d // 32, d_ff=f, seq=seq, micro_batch=mu))
+
+
+# FFN weights too wide for the transposed copies: input gradients on MN-major weights
+@pytest.mark.parametrize("seq,mu", [(33, 1), (100, 3)])
+def test_untransposed_weights(binding, seq, mu):  # noqa: F811
+    _check(binding, small_cfg("dh32_bf16", d_model=96, n_heads=3, d_ff=32768, seq=seq, micro_batch=mu))
 
 
 # fp32 products on 32 x 32, 64 x 64 (f 2080, and 4128: two rounds of 128 x 128 and a bit) and
