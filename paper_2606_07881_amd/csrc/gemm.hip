@@ -36,30 +36,21 @@ int cu_count() {
   return cus;
 }
 
-// fp32 products with a K-major A (forward, input gradients): 128 x 128 tiles when
-// their rounds over the CUs are at least 7/8 full, else 64 x 64, and 32 x 32 when
-// those are fewer than two per CU. A 32-deep k-tile of matrix work is 2.4, 0.7 and
-// 0.45 us at edge 128, 64 and 32 (the last two bound by the latency of the loads),
-// so 64 x 64 tiles do the same work at 1.1 to 1.2 of the time of full rounds and
-// win by sharing a partial one. us on 128 / 64 / 32 at K 512, NT and NN, by tiles of
-// 128 x 128: 256 of them 49 / 53 / 52 and 48 / 54 / 64; 384 78 / 67 / 75 and
-// 80 / 73 / 90; 448 78 / 78 / 86 and 80 / 87 / 105; 544 120 / 96 / 103 and
-// 120 / 105 / 125. A 256 x 128 product over 512 runs two 128 x 128 tiles on the
-// whole chip, or 32 of 32 x 32: 33 -> 8.4 us.
-// A single round over a short K costs its first loads and its epilogue: below K 256
-// the forward products (GEMM_NT) take 64 x 64 there too (256 tiles of 128 x 128, K 64
-// and 128: 14.1 / 13.2, 19.0 / 18.6; K 256 28.9 / 30.3), not the input gradients
-// (GEMM_NN: 11.9 / 13.9, 17.2 / 20.8).
-// Weight gradients (GEMM_TN) split K over idle CUs: the largest edge that gives two
-// workgroups per CU (2048 x 512 over 8192 rows 241 / 204 / 261, 1024 x 1024 over
-// 4096 170 / 115 / 134, 4096 x 1024 370 / 366 / 515).
-int gemm_f32_tile(GemmLayout lay, int M, int N, int K, int splits) {
-  const int64_t cus = cu_count();
-  auto tiles = [&](int e) { return (int64_t)((M + e - 1) / e) * ((N + e - 1) / e) * splits; };
-  const int64_t t = tiles(128), rounds = (t + cus - 1) / cus;
-  const bool brief = lay == GEMM_NT && rounds == 1 && K < 256;
-  if (lay == GEMM_TN ? t >= 2 * cus : 8 * t >= 7 * rounds * cus && !brief) return 128;
-  return tiles(64) >= 2 * cus ? 64 : 32;
+// fp32 products: the largest tile edge that still gives two workgroups per CU,
+// else the smallest. A 256 x 128 product over 512 runs two 128 x 128 tiles on
+// the whole chip, or 32 of 32 x 32: 33 -> 8.4 us a launch over its calls with
+// K 128 and 512 (matrix work is 2.4, 0.7 and 0.45 us per 32-deep k-tile at 128,
+// 64 and 32, the last two bound by the latency of the loads). us on 128 / 64 / 32
+// at K 512, forward and input gradient, by tiles of 128 x 128: 384 of them 78 / 67 /
+// 75 and 80 / 73 / 90; 512 79 / 86 / 97 and 80 / 97 / 118; weight gradients 2048 x
+// 512 over 8192 rows 241 / 204 / 261. A single whole round of 128 x 128 tiles is 2
+// to 9% faster than 64 x 64 (256 tiles: 49 / 53 / 52, 48 / 54 / 64) but not taken:
+// with one chain of sums for four a block's output is further from 64 bits (512 wide,
+// 2048 tokens: 1.5e-7 against 1.1e-7; 1024 wide, 4096 tokens: 5.9e-7 against 4.0e-7).
+int gemm_f32_tile(int M, int N, int splits) {
+  for (int e = 128; e > 32; e /= 2)
+    if ((int64_t)((M + e - 1) / e) * ((N + e - 1) / e) * splits >= 2 * cu_count()) return e;
+  return 32;
 }
 
 // Products with both operands K-major, by the rounds their tiles take on the CUs.
@@ -103,7 +94,10 @@ KmajorPlan gemm_kmajor_plan(int M, int N) {
 // rows: 3072 x 768 in 207 us with the three-stage ring on 256 x 128 tiles (two
 // rounds), 196 ping-pong, 172 on 252 of 256 x 256; 2304 x 768 170, 160, 138; 768
 // x 768 114, 112, 93. About 60 us of each are the atomic adds, which cross the
-// XCDs in memory.
+// XCDs in memory. All four products of a block of other widths, the ring's rule
+// (about 512 workgroups) and this one: 1024 946 and 791 us, 1280 1580 and 1123,
+// 1536 2197 and 1697, 1600 2495 and 1856, 1792 3032 and 2137; 512 over 16384 rows
+// 305 and 308.
 WindowPlan gemm_window_plan(int M, int N, int64_t K) {
   WindowPlan best{128, 1};
   double best_t = 1e30;
@@ -1533,7 +1527,7 @@ template <bool AK, bool BK, int EPI>
 hipError_t launch_f32(const GemmArgs& a, int splits, hipStream_t st) {
   if (a.seg_rows > 0) return hipErrorInvalidValue;
   hipError_t e;
-  switch (gemm_f32_tile(AK ? (BK ? GEMM_NT : GEMM_NN) : GEMM_TN, a.M, a.N, a.K, splits)) {
+  switch (gemm_f32_tile(a.M, a.N, splits)) {
     case 32: e = launch_cf<AK, BK, EPI, T32x32>(a, splits, st); break;
     case 64: e = launch_cf<AK, BK, EPI, T64x64>(a, splits, st); break;
     default: e = launch_cf<AK, BK, EPI, T128x128>(a, splits, st); break;
@@ -1829,7 +1823,7 @@ int gemm_acc_splits(DType dt, int M, int N, int K) {
   const int kt = (K + 31) / 32;
   return best_of([&](int sp) {
     if (sp > kt) return 1e30;
-    const int e = gemm_f32_tile(GEMM_TN, M, N, K, sp);
+    const int e = gemm_f32_tile(M, N, sp);
     const double tiles = (double)((M + e - 1) / e) * ((N + e - 1) / e), t_k = e == 128 ? 2.4 : e == 64 ? 0.7 : 0.45;
     return std::ceil(tiles * sp / (2 * cu_count())) * std::ceil((double)kt / sp) * t_k;
   });

@@ -120,7 +120,7 @@ hipError_t gemm_wgrad(DType dt, const GemmArgs& a, hipStream_t st);
 // splits > 1 is only valid with EPI_ATOMIC.
 hipError_t gemm(DType dt, bool out_f32, GemmLayout lay, GemmEpi epi, const GemmArgs& a, int splits, hipStream_t st);
 // Tile edge (128, 64 or 32) of an fp32 product.
-int gemm_f32_tile(GemmLayout lay, int M, int N, int K, int splits);
+int gemm_f32_tile(int M, int N, int splits);
 // Tiles of a bf16 product with both operands K-major. n1 > 0: columns [0, n1) and
 // the others are two launches, each on a plan of its own.
 enum KmajorTile { KT_256x128 = 0, KT_PP_256x256, KT_128x128, KT_128x64, KT_64x64 };

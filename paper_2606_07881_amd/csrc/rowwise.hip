@@ -411,7 +411,8 @@ __global__ void __launch_bounds__(NT) embed_fwd_kernel(const int32_t* __restrict
 // the micro-batch's mu sequences, up to 8 loads in flight, added to the token
 // rows of Gwte (atomically: ids repeat) and, summed in sequence order, to Gwpe.
 // One pass over dx for both; a workgroup's ids are uniform. Bound by the
-// atomic adds, which cross the XCDs in memory.
+// atomic adds, which cross the XCDs in memory: 8192 x 1024 in 29.9 us back to
+// back, 8.5 with the adds left out (37.9 in a pass, 38.2 + 7.0 as two kernels).
 template <typename T>
 __global__ void __launch_bounds__(NT) embed_bwd_kernel(const int32_t* __restrict__ ids, const T* __restrict__ dx,
                                                         float* Gwte, float* Gwpe, int mu, int S, int d, int V) {
