@@ -50,7 +50,7 @@ enum GemmEpi { EPI_STORE = 0, EPI_BIAS, EPI_BIAS_RES, EPI_BIAS_GELU, EPI_GELU_GR
 // a plain read-modify-write (no split, no atomics). `probs` is device memory
 // holding n problems; tile0 is the problem's first workgroup, a multiple of 8
 // (wgrad_group_tiles gives each problem's count; workgroups past a problem's
-// tiles exit). M_p, N_p, K multiples of 8 and 16-byte aligned operands.
+// tiles exit). M_p and N_p multiples of 8, any K, 16-byte aligned operands.
 // xcd_m: 0, or the number of row bands of the problem's tile grid when it is
 // split into 8 equal blocks (xcd_m bands x 8 / xcd_m column bands), one per XCD
 // (see wgrad_group_xcd_m).
